@@ -20,7 +20,9 @@ ARCH = os.environ.get("TFOCUS_ARCH", "gfx950")
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-I", os.path.join(HERE, "..", "include"), "-Wno-unused-command-line-argument"]
-PER_FILE = {"field_kernels.hip": ["-ffp-contract=off"],
+PER_FILE = {# no contraction (see the file), and no hoisting of machine loop invariants: the
+            # float64 constants of the trigonometry would fill 230 registers per thread
+            "field_kernels.hip": ["-ffp-contract=off", "-mllvm", "-disable-machine-licm"],
             # the z wave kernels of the shipped plans: memory-clause scheduling
             "fft_f32_zwave.hip": ["-mllvm", "-amdgpu-sched-strategy=max-memory-clause"]}
 

@@ -387,13 +387,18 @@ tf_status tf_batch_create(const tf_grid* grids, const tf_pulse* pulses, int32_t 
             break;
         }
         if (!all.empty()) {
-            st = alloc(&b->tabs[i], all.size() * sizeof(double));
-            if (st == TF_OK &&
-                hipMemcpy(b->tabs[i], all.data(), all.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess)
+            const int npoly = pulse_npoly(&pulses[i], all, nfreq);
+            const size_t poly_len = pulse_table_doubles(all, npoly) - all.size();
+            st = alloc(&b->tabs[i], (poly_len + all.size()) * sizeof(double));
+            double* dev = static_cast<double*>(b->tabs[i]);
+            if (st == TF_OK && hipMemcpy(dev + poly_len, all.data(), all.size() * sizeof(double), hipMemcpyHostToDevice) !=
+                                   hipSuccess)
                 st = fail(TF_EDEVICE, "pulse table upload failed");
-            if (st == TF_OK)
-                pulse_dev_tables(b->pdev[i], &pulses[i], static_cast<const double*>(b->tabs[i]), spec_len, gnorm,
-                                 nfreq);
+            if (st == TF_OK) {
+                pulse_dev_tables(b->pdev[i], &pulses[i], dev, spec_len, gnorm, nfreq, npoly);
+                if (npoly > 0 && tf::launch_spec_poly(dev, b->pdev[i], b->stream) != hipSuccess)
+                    st = fail(TF_EDEVICE, "pulse table launch failed");
+            }
         }
     }
     if (st != TF_OK) {

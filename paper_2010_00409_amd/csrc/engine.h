@@ -211,16 +211,34 @@ inline tf_status pulse_tables(const tf_pulse* pulse, std::vector<double>& all, s
     return TF_OK;
 }
 
-// Points the descriptor at a device copy of pulse_tables' output.
+// Interval polynomials (launch_spec_poly) a spectral pulse's init uses; 0: none.
+inline int pulse_npoly(const tf_pulse* pulse, const std::vector<double>& all, int nfreq) {
+    if (pulse->envelope != TF_ENV_SPECTRAL) return 0;
+    return spec_poly_count(pulse->L, all[0] + all[1] * (nfreq - 1));
+}
+
+// Doubles of a pulse's device tables: the interval polynomials (first, for
+// their alignment), then pulse_tables' output.
+inline size_t pulse_table_doubles(const std::vector<double>& all, int npoly) {
+    return (size_t)npoly * 2 * SPEC_COEF + all.size();
+}
+
+// Points the descriptor at the pulse's device tables: npoly interval
+// polynomials (filled by the caller with launch_spec_poly), then a copy of
+// pulse_tables' output.
 inline void pulse_dev_tables(PulseDev& p, const tf_pulse* pulse, const double* dev, size_t spec_len, double gnorm,
-                             int nfreq) {
+                             int nfreq, int npoly) {
+    const double* tab = dev + (size_t)npoly * 2 * SPEC_COEF;
     if (pulse->envelope == TF_ENV_SPECTRAL) {
-        p.spec = dev;
+        p.spec = tab;
         p.nfreq = nfreq;
         p.gnorm = gnorm;
+        p.poly = dev;
+        p.npoly = npoly;
+        p.poly_inv = npoly / pulse->L;
     }
     p.nbumps = pulse->nbumps;
-    p.bumps = pulse->nbumps > 0 ? dev + spec_len : nullptr;
+    p.bumps = pulse->nbumps > 0 ? tab + spec_len : nullptr;
 }
 
 // Device pulse descriptor; the spectral table (nfreq x {w, a, phi}) must be
@@ -240,6 +258,16 @@ inline PulseDev pulse_dev(const tf_pulse* pulse, const tf_pulse_info& g) {
     p.alpha_max = g.alpha_max;
     p.cep = pulse->cep;
     p.gnorm = 1.0;
+    // support along x (k_init_map): alpha <= alpha_max means -x >= rho
+    // cot(alpha_max), and R >= R_min then -x >= R_min cos(alpha_max) while
+    // the cosine is positive; apertures near or past pi have no bound.  An
+    // infinite cotangent makes its comparison false at every rho, 0 included.
+    const double inf = HUGE_VAL;
+    const bool wide = g.alpha_max > 3.1;
+    p.cot_max = wide ? -inf : 1.0 / std::tan(g.alpha_max);
+    p.x_rc = !wide && g.alpha_max < 0.5 * M_PI ? g.R_min * std::cos(g.alpha_max) : -inf;
+    const double lo = g.theta - 0.5 * pulse->eps;
+    p.cot_lo = pulse->transverse == TF_TS_FLATTOP && lo > 0.0 && lo < 3.1 ? 1.0 / std::tan(lo) : inf;
     if (pulse->polarization == TF_POL_RADIAL) {
         p.nparts = 1;
         p.amp[0] = 1.0;

@@ -26,8 +26,8 @@ __device__ double u_ts(double alpha, const PulseDev& p) {
 // Longitudinal profile with carrier, zeta inside [-L/2, L/2] (checked by the
 // caller), for the cos^2 envelope of Eq. (7) and the Gaussian envelope of
 // Sec. III.B.1.
-__device__ double u_l_closed(double zeta, double phase, const PulseDev& p) {
-    if (p.envelope == 0) {
+template <int ENV> __device__ __forceinline__ double u_l_closed(double zeta, double phase, const PulseDev& p) {
+    if constexpr (ENV == 0) {
         const double c = cos(M_PI * zeta / p.L);
         return sin(2.0 * M_PI * zeta / p.lambda - phase) * (c * c);
     }
@@ -56,6 +56,66 @@ __device__ void spectral_sum(double zeta, const PulseDev& p, double& sr, double&
     si = pr * es + pim * ec;
 }
 
+// The same sum from the interval polynomials: zeta in [-L/2, L/2] falls in
+// interval q at t in [-1, 1) half widths from its centre, and S is the
+// degree-7 Taylor polynomial in t with the interval's 8 complex
+// coefficients: one 128-byte line and 14 fused multiply-adds per node in
+// place of Horner's rule over all (about 200) samples.
+__device__ __forceinline__ void spectral_poly(double zeta, const PulseDev& p, double& sr, double& si) {
+    const double s = (zeta + 0.5 * p.L) * p.poly_inv;
+    int q = (int)s;
+    q = q < 0 ? 0 : (q >= p.npoly ? p.npoly - 1 : q);
+    const double t = 2.0 * (s - q) - 1.0;
+    const double2* c = reinterpret_cast<const double2*>(p.poly) + q * SPEC_COEF;
+    double2 r = c[SPEC_COEF - 1];
+#pragma unroll
+    for (int k = SPEC_COEF - 2; k >= 0; --k) {
+        const double2 ck = c[k];
+        r.x = fma(r.x, t, ck.x);
+        r.y = fma(r.y, t, ck.y);
+    }
+    sr = r.x;
+    si = r.y;
+}
+
+// Coefficients of one interval per wave: lane m takes the samples m, m + 64,
+// ... and adds c_m exp(-i w_m zc) (-i w_m h)^k / k! (h the half width, zc
+// the centre), then the lanes are summed.  The phase w_m zc is the exact
+// product (its rounding error is put back to first order).
+__global__ __launch_bounds__(64) void k_spec_poly(double* __restrict__ poly, PulseDev p) {
+    const int q = blockIdx.x, lane = threadIdx.x;
+    const double h = 0.5 * p.L / p.npoly;
+    const double zc = fma((double)(2 * q + 1), h, -0.5 * p.L);
+    double a[2 * SPEC_COEF];
+#pragma unroll
+    for (int k = 0; k < 2 * SPEC_COEF; ++k) a[k] = 0.0;
+    for (int m = lane; m < p.nfreq; m += 64) {
+        const double w = fma((double)m, p.spec[1], p.spec[0]);
+        const double ph = w * zc, err = fma(w, zc, -ph);
+        double sn, cs;
+        sincos(ph, &sn, &cs);
+        const double ec = fma(-err, sn, cs), es = -fma(err, cs, sn);     // exp(-i w zc)
+        const double cr = p.spec[2 + 2 * m], ci = p.spec[3 + 2 * m];
+        double vr = fma(cr, ec, -(ci * es)), vi = fma(cr, es, ci * ec);
+        const double wh = w * h;
+#pragma unroll
+        for (int k = 0; k < SPEC_COEF; ++k) {
+            a[2 * k] += vr;
+            a[2 * k + 1] += vi;
+            const double f = wh / (k + 1), t = vr;                        // times -i wh / (k + 1)
+            vr = vi * f;
+            vi = -t * f;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 2 * SPEC_COEF; ++k)
+        for (int off = 32; off > 0; off >>= 1) a[k] += __shfl_xor(a[k], off);
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < 2 * SPEC_COEF; ++k) poly[(long)q * 2 * SPEC_COEF + k] = a[k];
+    }
+}
+
 // Wavefront phase of the direction (alpha, azimuth): a sum of Gaussian bumps
 // over the angular position (ay, az) = alpha (y, z) / rho (Sec. III.B.3).
 __device__ double bump_phase(double alpha, double y, double z, double rho, const PulseDev& p) {
@@ -70,26 +130,44 @@ __device__ double bump_phase(double alpha, double y, double z, double rho, const
     return ph;
 }
 
-// Adds the unmapped pulse at physical point (x, y, z) to e, b.
-__device__ void add_pulse(double x, double y, double z, const PulseDev& p, double* e, double* b) {
+// Adds the unmapped pulse at physical point (x, y, z), rho = sqrt(y^2 + z^2),
+// to e, b.  Points clearly outside the aperture, and points clearly inside
+// the flat part of a flat-top aperture, are told by -x against rho
+// cot(angle) (1e-9 R to the safe side); the angle itself is evaluated only
+// for the others and where the profile needs it.  ENV and BUMPS are template
+// parameters because the float64 trigonometry of the profiles not in use
+// would otherwise take registers in every variant.
+enum EnvKind { ENV_COS2 = 0, ENV_GAUSS = 1, ENV_SUM = 2, ENV_POLY = 3 };
+template <int ENV, bool BUMPS>
+__device__ __forceinline__ void add_pulse(double x, double y, double z, double rho, const PulseDev& p, double* e, double* b) {
     const double R = sqrt(x * x + y * y + z * z);
     const double zeta = R - p.R0;
     if (!(zeta >= -0.5 * p.L && zeta <= 0.5 * p.L)) return;
-    const double rho = sqrt(y * y + z * z);
-    const double alpha = atan2(rho, -x);                    // angle from the -x axis
-    if (!(alpha <= p.alpha_max)) return;
-    const double ts = u_ts(alpha, p);
-    double sr = 0.0, si = 0.0;
-    if (p.envelope == 2) spectral_sum(zeta, p, sr, si);     // shared by both polarisation parts
+    const double tol = 1e-9 * R;
+    if (-x < rho * p.cot_max - tol) return;
+    double ts = 1.0, alpha = 0.0;
+    if (BUMPS || !(-x > rho * p.cot_lo + tol)) {
+        alpha = atan2(rho, -x);                             // angle from the -x axis
+        if (!(alpha <= p.alpha_max)) return;
+        ts = u_ts(alpha, p);
+    }
+    double sr = 0.0, si = 0.0;                              // shared by both polarisation parts
+    if constexpr (ENV == ENV_POLY) spectral_poly(zeta, p, sr, si);
+    if constexpr (ENV == ENV_SUM) spectral_sum(zeta, p, sr, si);
     // the perturbation adds to every part's carrier phase, as the CEP does
-    const double dph = p.nbumps > 0 ? bump_phase(alpha, y, z, rho, p) : 0.0;
-    double cb = 1.0, sb = 0.0;
-    if (p.nbumps > 0 && p.envelope == 2) sincos(dph, &sb, &cb);
+    double dph = 0.0, cb = 1.0, sb = 0.0;
+    if constexpr (BUMPS) {
+        dph = bump_phase(alpha, y, z, rho, p);
+        if constexpr (ENV >= ENV_SUM) sincos(dph, &sb, &cb);
+    }
+    const double iR = 1.0 / R;
     for (int k = 0; k < p.nparts; ++k) {
-        const double ul = p.envelope == 2
-                              ? ((p.cph[k] * cb - p.sph[k] * sb) * sr - (p.sph[k] * cb + p.cph[k] * sb) * si) / p.gnorm
-                              : u_l_closed(zeta, p.cep + p.phase_off[k] + dph, p);
-        const double u = p.A / R * ul * ts;
+        double ul;
+        if constexpr (ENV >= ENV_SUM)
+            ul = ((p.cph[k] * cb - p.sph[k] * sb) * sr - (p.sph[k] * cb + p.cph[k] * sb) * si) / p.gnorm;
+        else
+            ul = u_l_closed<ENV>(zeta, p.cep + p.phase_off[k] + dph, p);
+        const double u = p.A * iR * ul * ts;
         const double* d = p.d[k];
         // s1 ~ d x R, s0 ~ R x (d x R)
         const double c1x = d[1] * z - d[2] * y, c1y = d[2] * x - d[0] * z, c1z = d[0] * y - d[1] * x;
@@ -97,52 +175,93 @@ __device__ void add_pulse(double x, double y, double z, const PulseDev& p, doubl
         if (!(n1 > 0.0)) continue;
         const double c0x = y * c1z - z * c1y, c0y = z * c1x - x * c1z, c0z = x * c1y - y * c1x;
         const double au = p.amp[k] * u;
-        const double i1 = 1.0 / n1, i0 = 1.0 / (n1 * R);
+        const double i1 = 1.0 / n1, i0 = i1 * iR;
         e[0] += au * c0x * i0; e[1] += au * c0y * i0; e[2] += au * c0z * i0;
         b[0] += au * c1x * i1; b[1] += au * c1y * i1; b[2] += au * c1z * i1;
     }
 }
 
-// One thread per layer node: sum of the pulse over the preimages x + n D,
-// n ascending (Eq. (13) inverted; overlapping replicas superpose); with
-// transverse replication also over y + m Dy, z + l Dz (l, then m ascending
-// outside the x preimages).
-template <typename T>
-__global__ __launch_bounds__(256) void k_init_map(T* __restrict__ state, GridDev g, PulseDev p) {
-    const long cells = (long)g.nx * g.ny * g.nz;
-    const long id = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= cells) return;
-    const int i = (int)(id % g.nx);
-    const int j = (int)((id / g.nx) % g.ny);
-    const int k = (int)(id / ((long)g.nx * g.ny));
+// Layer nodes: sum of the pulse over the preimages x + n D, n ascending
+// (Eq. (13) inverted; overlapping replicas superpose); with transverse
+// replication also over y + m Dy, z + l Dz (l, then m ascending outside the
+// x preimages).  A thread takes V consecutive nodes of a row (16 bytes of
+// each component; every supported nx is a multiple of 8), so the row's
+// geometry is evaluated once for them.  At a given rho the support is an
+// interval of x, [-sqrt(R_max^2 - rho^2), -max(rho cot(alpha_max), x_rc)], so
+// only the one or two n that reach it are tried (1e-9 R_max to the safe
+// side; add_pulse decides).  Bound by float64 arithmetic (geometry and the
+// interval polynomial) in float32, by the stores in float64.  MI355X, before
+// (a node per thread, every preimage tried, the sum over all samples) and
+// now: spectral 96 x 256 x 256 float32 765 -> 88 us, 512^3 4870 -> 826 us;
+// cos^2 128 x 1024^2 float32 2142 -> 735 us, 112 x 896^2 float64 1652 -> 690
+// us (6.2 TB/s).  One or two nodes per thread: 512^3 1.7 and 1.4 times this
+// layout's time.  Four blocks per CU (128 registers) for the polynomial
+// (887 -> 826 us); the others would spill.
+template <typename T, int ENV, bool BUMPS>
+__global__ __launch_bounds__(256, ENV == ENV_POLY && !BUMPS ? 4 : 1) void k_init_map(T* __restrict__ state, GridDev g, PulseDev p) {
+    constexpr int V = 16 / sizeof(T);
+    typedef T vec __attribute__((ext_vector_type(V)));
+    const unsigned vx = (unsigned)g.nx / V;
+    const unsigned id = blockIdx.x * 256u + threadIdx.x;       // at most 2^30 nodes (1024 per axis)
+    const unsigned row = id / vx;
+    if (row >= (unsigned)g.ny * (unsigned)g.nz) return;
+    const int i = (int)(id - row * vx) * V;
+    const int k = (int)(row / (unsigned)g.ny);
+    const int j = (int)(row - (unsigned)k * (unsigned)g.ny);
     const double D = g.nx * g.dx;
-    const double xt = g.x_min + i * g.dx;
     const double y = g.y_min + j * g.dy;
     const double z = g.z_min + k * g.dz;
-    const double Rmax = p.R0 + 0.5 * p.L;
-    double e[3] = {0.0, 0.0, 0.0}, b[3] = {0.0, 0.0, 0.0};
-    const long n0 = (long)floor((-Rmax - xt) / D) - 1;
-    const long n1 = (long)ceil((Rmax - xt) / D) + 1;
-    long m0 = 0, m1 = 0, l0 = 0, l1 = 0;
+    const double Rmax = p.R0 + 0.5 * p.L, slack = 1e-9 * Rmax, iD = 1.0 / D;
     const double Dy = g.ny * g.dy, Dz = g.nz * g.dz;
+    long m0 = 0, m1 = 0, l0 = 0, l1 = 0;
     if (g.rep_yz) {
         m0 = (long)floor((-Rmax - y) / Dy) - 1;
         m1 = (long)ceil((Rmax - y) / Dy) + 1;
         l0 = (long)floor((-Rmax - z) / Dz) - 1;
         l1 = (long)ceil((Rmax - z) / Dz) + 1;
     }
-    for (long l = l0; l <= l1; ++l)
-        for (long m = m0; m <= m1; ++m) {
-            const double yy = g.rep_yz ? y + m * Dy : y, zz = g.rep_yz ? z + l * Dz : z;
-            if (yy * yy + zz * zz <= Rmax * Rmax)
-                for (long n = n0; n <= n1; ++n) add_pulse(xt + n * D, yy, zz, p, e, b);
+    // the x range of the support at a transverse point; empty (lo > hi) outside R_max
+    auto support = [&](double yy, double zz, double& rho, double& lo, double& hi) {
+        const double rho2 = yy * yy + zz * zz;
+        lo = 1.0; hi = -1.0; rho = 0.0;
+        if (rho2 <= Rmax * Rmax) {
+            rho = sqrt(rho2);
+            const double xm = sqrt(Rmax * Rmax - rho2);
+            lo = -xm - slack;
+            hi = fmin(xm, -fmax(rho * p.cot_max, p.x_rc)) + slack;
         }
-    state[0 * cells + id] = T(e[0]);
-    state[1 * cells + id] = T(e[1]);
-    state[2 * cells + id] = T(e[2]);
-    state[3 * cells + id] = T(b[0]);
-    state[4 * cells + id] = T(b[1]);
-    state[5 * cells + id] = T(b[2]);
+    };
+    double rho, lo, hi;
+    if (!g.rep_yz) support(y, z, rho, lo, hi);
+    vec o[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c)
+#pragma unroll
+        for (int v = 0; v < V; ++v) o[c][v] = T(0);
+#pragma unroll 1
+    for (int v = 0; v < V; ++v) {
+        const double xt = g.x_min + (i + v) * g.dx;
+        double e[3] = {0.0, 0.0, 0.0}, b[3] = {0.0, 0.0, 0.0};
+        for (long l = l0; l <= l1; ++l)
+            for (long m = m0; m <= m1; ++m) {
+                const double yy = g.rep_yz ? y + m * Dy : y, zz = g.rep_yz ? z + l * Dz : z;
+                if (g.rep_yz) support(yy, zz, rho, lo, hi);
+                if (lo <= hi) {
+                    const long n0 = (long)ceil((lo - xt) * iD), n1 = (long)floor((hi - xt) * iD);
+                    for (long n = n0; n <= n1; ++n) add_pulse<ENV, BUMPS>(xt + n * D, yy, zz, rho, p, e, b);
+                }
+            }
+        // one copy of the pulse's code for all V nodes: the node's results
+        // are selected into its place
+#pragma unroll
+        for (int c = 0; c < 6; ++c)
+#pragma unroll
+            for (int w = 0; w < V; ++w) o[c][w] = w == v ? T(c < 3 ? e[c] : b[c - 3]) : o[c][w];
+    }
+    const size_t cells = (size_t)g.nx * g.ny * g.nz;
+    T* dst = state + (size_t)row * g.nx + i;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) *reinterpret_cast<vec*>(dst + c * cells) = o[c];
 }
 
 // ---------------------------------------------------------------- cut-out
@@ -229,9 +348,26 @@ __global__ __launch_bounds__(256) void k_reduce(const double* __restrict__ part,
 // ---------------------------------------------------------------- launchers
 template <typename T>
 hipError_t launch_init_map(T* state, const GridDev& g, const PulseDev& p, hipStream_t st) {
-    const long cells = (long)g.nx * g.ny * g.nz;
-    const unsigned nb = (unsigned)((cells + 255) / 256);
-    hipLaunchKernelGGL(k_init_map<T>, dim3(nb), dim3(256), 0, st, state, g, p);
+    const long items = (long)g.nx * g.ny * g.nz / (16 / sizeof(T));
+    const unsigned nb = (unsigned)((items + 255) / 256);
+    const int env = p.envelope == 0 ? ENV_COS2 : p.envelope == 1 ? ENV_GAUSS : p.npoly > 0 ? ENV_POLY : ENV_SUM;
+#define TF_INIT(E)                                                                                          \
+    case E:                                                                                                 \
+        if (p.nbumps > 0) hipLaunchKernelGGL((k_init_map<T, E, true>), dim3(nb), dim3(256), 0, st, state, g, p); \
+        else hipLaunchKernelGGL((k_init_map<T, E, false>), dim3(nb), dim3(256), 0, st, state, g, p);        \
+        break;
+    switch (env) {
+        TF_INIT(ENV_COS2)
+        TF_INIT(ENV_GAUSS)
+        TF_INIT(ENV_SUM)
+        TF_INIT(ENV_POLY)
+    }
+#undef TF_INIT
+    return hipGetLastError();
+}
+
+hipError_t launch_spec_poly(double* poly, const PulseDev& p, hipStream_t st) {
+    hipLaunchKernelGGL(k_spec_poly, dim3(p.npoly), dim3(64), 0, st, poly, p);
     return hipGetLastError();
 }
 

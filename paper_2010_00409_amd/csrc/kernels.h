@@ -117,6 +117,16 @@ struct PulseDev {
     // spectral only: {w0, dw, then c_m = a_m exp(i phi_m) as re, im} for the
     // nfreq kept samples w_m = w0 + m dw
     const double* spec;
+    // spectral only, npoly > 0: the sampled spectrum's sum over [-L/2, L/2]
+    // as npoly Taylor polynomials (launch_spec_poly); interval q covers
+    // zeta + L/2 in [q, q + 1) / poly_inv
+    const double* poly;
+    int npoly;
+    double poly_inv;
+    // bounds of the support along x at a given rho: -x >= rho cot(alpha_max)
+    // and -x >= x_rc; flat-top: -x > rho cot_lo lies inside the first window
+    // of Eq. (5)
+    double cot_max, x_rc, cot_lo;
     // wavefront phase bumps {ay, az, amplitude, width} (nbumps of them)
     int nbumps;
     const double* bumps;
@@ -127,6 +137,21 @@ struct GridDev {
     double dx, dy, dz, x_min, y_min, z_min;
     int rep_yz;                   // y and z are periods of the mapping too
 };
+
+// Interval polynomials of a sampled spectrum: SPEC_COEF complex Taylor
+// coefficients per interval (one 128-byte line), intervals of half width
+// theta / w_max with theta <= SPEC_THETA, so the truncation
+// theta^8 / 8! stays below 2.3e-17 of sum |a_m|.
+constexpr int SPEC_COEF = 8;
+constexpr double SPEC_THETA = 1.0 / 32;
+constexpr int SPEC_MAX_POLY = 1 << 15;    // 4 MB of coefficients; longer windows take the direct sum
+// intervals for a window of length L and a largest frequency w_max; 0: too many
+inline int spec_poly_count(double L, double w_max) {
+    const double n = L * w_max / (2.0 * SPEC_THETA) + 1.0;
+    return n < (double)SPEC_MAX_POLY ? (int)n : 0;
+}
+// Fills p.npoly intervals of coefficients at poly (p.spec, p.nfreq, p.L, p.npoly set).
+hipError_t launch_spec_poly(double* poly, const PulseDev& p, hipStream_t st);
 
 template <typename T> hipError_t launch_init_map(T* state, const GridDev& g, const PulseDev& p,
                                                  hipStream_t st);

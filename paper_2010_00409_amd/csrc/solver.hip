@@ -37,7 +37,8 @@ struct tf_solver {
     double* partials = nullptr;
     size_t npartials = 0;
     double* results = nullptr;     // 8 doubles
-    void* pulse_tab = nullptr;
+    void* pulse_tab = nullptr;     // device tables of the last pulse, kept for the next
+    size_t pulse_tab_len = 0;      // its size in doubles
     void* dcbuf = nullptr;         // diagnostics: packed kx = 0 slot after the forward z FFT
     tf::RowMap rm{};
     bool fast = true;              // use the specialised float32 column kernels
@@ -468,16 +469,23 @@ tf_status tf_set_pulse(tf_solver* s, const tf_pulse* pulse, tf_pulse_info* info)
     st = pulse_tables(pulse, all, spec_len, gnorm, nfreq);
     if (st != TF_OK) return st;
     if (!all.empty()) {
-        if (s->pulse_tab) {
-            TF_HIP(hipStreamSynchronize(s->stream));
-            TF_HIP(hipFree(s->pulse_tab));
-            s->pulse_tab = nullptr;
+        const int npoly = pulse_npoly(pulse, all, nfreq);
+        const size_t len = pulse_table_doubles(all, npoly), poly_len = len - all.size();
+        if (s->pulse_tab_len < len) {
+            if (s->pulse_tab) {
+                TF_HIP(hipStreamSynchronize(s->stream));
+                TF_HIP(hipFree(s->pulse_tab));
+                s->pulse_tab = nullptr;
+                s->pulse_tab_len = 0;
+            }
+            TF_HIP(hipMalloc(&s->pulse_tab, len * sizeof(double)));
+            s->pulse_tab_len = len;
         }
-        TF_HIP(hipMalloc(&s->pulse_tab, all.size() * sizeof(double)));
-        TF_HIP(hipMemcpyAsync(s->pulse_tab, all.data(), all.size() * sizeof(double), hipMemcpyHostToDevice,
-                              s->stream));
+        double* dev = static_cast<double*>(s->pulse_tab);
+        TF_HIP(hipMemcpyAsync(dev + poly_len, all.data(), all.size() * sizeof(double), hipMemcpyHostToDevice, s->stream));
         TF_HIP(hipStreamSynchronize(s->stream));
-        pulse_dev_tables(p, pulse, static_cast<const double*>(s->pulse_tab), spec_len, gnorm, nfreq);
+        pulse_dev_tables(p, pulse, dev, spec_len, gnorm, nfreq, npoly);
+        if (npoly > 0) TF_HIP(tf::launch_spec_poly(dev, p, s->stream));
     }
     tf::GridDev gd = grid_dev(s->grid);
     hipError_t e = timed(s, TF_PASS_INIT, [&] {
