@@ -141,8 +141,9 @@ struct Group {
     std::vector<int> slot_of;        // slot -> instance id (for the current run)
     long cells = 0;
     size_t state_elems = 0, spec_elems = 0;   // per slot
-    void* state = nullptr;
+    void* state = nullptr;           // state and spec: blocks of the cache, with their sizes
     void* spec = nullptr;
+    size_t state_bytes = 0, spec_bytes = 0;
     void* tw[3] = {nullptr, nullptr, nullptr};
     double* cdt = nullptr;           // per slot
     tf::RowMap rm{};
@@ -163,7 +164,7 @@ struct tf_batch {
     std::vector<tf_pulse_info> infos;
     std::vector<int> group_of, slot_in_group;
     std::vector<Group> groups;
-    std::vector<void*> tabs;               // per instance spectral table (or null)
+    void* tabs = nullptr;                  // pulse tables of all instances
     std::vector<tf::PulseDev> pdev;
     hipEvent_t fork = nullptr;
     hipStream_t cap = nullptr;             // private stream the sweep is captured on
@@ -180,14 +181,15 @@ namespace {
 void batch_free(tf_batch* b) {
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     for (Group& g : b->groups) {
-        void* ps[] = {g.state, g.spec, g.tw[0], g.tw[1], g.tw[2], g.cdt};
+        BlockCache::get().put(g.state, g.state_bytes);
+        BlockCache::get().put(g.spec, g.spec_bytes);
+        void* ps[] = {g.tw[0], g.tw[1], g.tw[2], g.cdt};
         for (void* p : ps)
             if (p) (void)hipFree(p);
         if (g.stream) (void)hipStreamDestroy(g.stream);
         if (g.done) (void)hipEventDestroy(g.done);
     }
-    for (void* t : b->tabs)
-        if (t) (void)hipFree(t);
+    if (b->tabs) (void)hipFree(b->tabs);
     if (b->fork) (void)hipEventDestroy(b->fork);
     if (b->cap) (void)hipStreamDestroy(b->cap);
 }
@@ -308,7 +310,6 @@ tf_status tf_batch_create(const tf_grid* grids, const tf_pulse* pulses, int32_t 
     b->pulses.assign(pulses, pulses + n);
     b->infos.resize(n);
     b->group_of.resize(n);
-    b->tabs.assign(n, nullptr);
     b->pdev.resize(n);
     size_t need = 0;
     for (int i = 0; i < n; ++i) {
@@ -342,8 +343,8 @@ tf_status tf_batch_create(const tf_grid* grids, const tf_pulse* pulses, int32_t 
         delete b;
         return fail(TF_ENOMEM, "batch needs " + std::to_string(need) + " device bytes, above TFOCUS_MAX_DEVICE_BYTES");
     }
-    auto alloc = [&](void** p, size_t bytes) -> tf_status {
-        hipError_t e = hipMalloc(p, bytes);
+    auto alloc = [&](void** p, size_t bytes, size_t* got = nullptr) -> tf_status {
+        hipError_t e = got ? BlockCache::get().take(p, bytes, got) : hipMalloc(p, bytes);
         if (e == hipErrorOutOfMemory) return fail(TF_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
         if (e != hipSuccess) return fail(TF_EDEVICE, std::string("hipMalloc: ") + hipGetErrorString(e));
         return TF_OK;
@@ -358,8 +359,8 @@ tf_status tf_batch_create(const tf_grid* grids, const tf_pulse* pulses, int32_t 
         G.kp = plan_for(g, precision);
         G.rm = tf::RowMap(g.ny, g.nz, G.kp.row_block);
         const size_t m = G.members.size();
-        st = alloc(&G.state, m * G.state_elems * b->esize);
-        if (st == TF_OK) st = alloc(&G.spec, m * G.spec_elems * b->esize);
+        st = alloc(&G.state, m * G.state_elems * b->esize, &G.state_bytes);
+        if (st == TF_OK) st = alloc(&G.spec, m * G.spec_elems * b->esize, &G.spec_bytes);
         const int ns[3] = {g.nx, g.ny, g.nz};
         for (int a = 0; a < 3 && st == TF_OK; ++a) st = alloc(&G.tw[a], 2 * b->esize * ns[a]);
         if (st == TF_OK) st = alloc((void**)&G.cdt, m * sizeof(double));
@@ -375,30 +376,37 @@ tf_status tf_batch_create(const tf_grid* grids, const tf_pulse* pulses, int32_t 
         st = fail(TF_EDEVICE, "hipEventCreate failed");
     if (st == TF_OK && hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking) != hipSuccess)
         st = fail(TF_EDEVICE, "hipStreamCreate failed");
+    // pulse tables of every instance: one allocation, one upload
+    std::vector<double> host;
+    std::vector<size_t> off(n, 0), at(n, 0), spec_len(n, 0);   // device offset, offset in host, spectral part
+    std::vector<double> gnorm(n, 1.0);
+    std::vector<int> nfreq(n, 0), npoly(n, 0);
+    size_t polys = 0;
     for (int i = 0; i < n && st == TF_OK; ++i) {
         b->pdev[i] = pulse_dev(&pulses[i], b->infos[i]);
         std::vector<double> all;
-        size_t spec_len = 0;
-        double gnorm = 1.0;
-        int nfreq = 0;
-        st = pulse_tables(&pulses[i], all, spec_len, gnorm, nfreq);
+        st = pulse_tables(&pulses[i], all, spec_len[i], gnorm[i], nfreq[i]);
         if (st != TF_OK) {
             st = fail(st, "instance " + std::to_string(i) + ": " + last_error());
             break;
         }
-        if (!all.empty()) {
-            const int npoly = pulse_npoly(&pulses[i], all, nfreq);
-            const size_t poly_len = pulse_table_doubles(all, npoly) - all.size();
-            st = alloc(&b->tabs[i], (poly_len + all.size()) * sizeof(double));
-            double* dev = static_cast<double*>(b->tabs[i]);
-            if (st == TF_OK && hipMemcpy(dev + poly_len, all.data(), all.size() * sizeof(double), hipMemcpyHostToDevice) !=
-                                   hipSuccess)
-                st = fail(TF_EDEVICE, "pulse table upload failed");
-            if (st == TF_OK) {
-                pulse_dev_tables(b->pdev[i], &pulses[i], dev, spec_len, gnorm, nfreq, npoly);
-                if (npoly > 0 && tf::launch_spec_poly(dev, b->pdev[i], b->stream) != hipSuccess)
-                    st = fail(TF_EDEVICE, "pulse table launch failed");
-            }
+        if (!all.empty()) npoly[i] = pulse_npoly(&pulses[i], all, nfreq[i]);
+        off[i] = polys;
+        polys += (size_t)npoly[i] * 2 * tf::SPEC_COEF;
+        at[i] = host.size();
+        host.insert(host.end(), all.begin(), all.end());
+    }
+    if (st == TF_OK && !host.empty()) {
+        st = alloc(&b->tabs, (polys + host.size()) * sizeof(double));
+        double* dev = static_cast<double*>(b->tabs);
+        if (st == TF_OK &&
+            hipMemcpy(dev + polys, host.data(), host.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess)
+            st = fail(TF_EDEVICE, "pulse table upload failed");
+        for (int i = 0; i < n && st == TF_OK; ++i) {
+            pulse_dev_tables(b->pdev[i], &pulses[i], dev + off[i], dev + polys + at[i], spec_len[i], gnorm[i], nfreq[i],
+                             npoly[i]);
+            if (npoly[i] > 0 && tf::launch_spec_poly(dev + off[i], b->pdev[i], b->stream) != hipSuccess)
+                st = fail(TF_EDEVICE, "pulse table launch failed");
         }
     }
     if (st != TF_OK) {

@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -39,18 +40,75 @@ inline bool length_ok(int n) {
 
 inline bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 
+// ---- device blocks kept from one solver or batch for the next ----
+
+// Large device allocations of destroyed solvers and batches, kept for the
+// next one of about the same size: a freed block's pages are wiped and
+// mapped anew at about 35 GB/s, which made the allocation of a 64-window
+// batch (19 GB) cost some 15 times its kernels.  A block enters after the
+// device has been synchronised (what hipFree would do), so no queued work
+// of any stream still uses it.  Bounds: blocks of 32 MB and more, an eighth
+// of the device's memory in all; a block that four later requests pass over
+// is given back, all are when an allocation fails, and when a surrogate is
+// created (the next consumer of the windows a batch made).  One mutex: any
+// thread may create and destroy objects.
+class BlockCache {
+public:
+    static BlockCache& get();
+    // A block of at least `bytes` on the current device; *got its size.
+    hipError_t take(void** ptr, size_t bytes, size_t* got);
+    // Back into the cache (or to the device, where it does not fit the bounds).
+    void put(void* ptr, size_t bytes);
+    // Give every kept block back.
+    void clear();
+
+private:
+    struct Block { int dev; void* ptr; size_t bytes; int passed; };
+    std::mutex mu_;
+    std::vector<Block> free_;
+    void clear_locked();
+};
+
 // ---- pulse geometry (host, float64) ----
 
-// F(theta0) = int_0^pi sin(a) exp(-2 a^2 / theta0^2) da by composite Simpson
-// on [0, min(pi, 12 theta0)] (the integrand is below e^-288 beyond).
+// Nodes and weights of the 16-point Gauss-Legendre rule on [-1, 1] (Newton's
+// iteration on P_16 from the Chebyshev-like starting points).
+struct Gauss16 {
+    double x[16], w[16];
+    Gauss16() {
+        for (int i = 0; i < 16; ++i) {
+            double t = std::cos(M_PI * (i + 0.75) / 16.5), dp = 1.0;
+            for (int it = 0; it < 8; ++it) {
+                double p0 = 1.0, p1 = t;
+                for (int n = 2; n <= 16; ++n) {
+                    const double p2 = ((2 * n - 1) * t * p1 - (n - 1) * p0) / n;
+                    p0 = p1;
+                    p1 = p2;
+                }
+                dp = 16.0 * (t * p1 - p0) / (t * t - 1.0);
+                t -= p1 / dp;
+            }
+            x[i] = t;
+            w[i] = 2.0 / ((1.0 - t * t) * dp * dp);
+        }
+    }
+};
+
+// F(theta0) = int_0^pi sin(a) exp(-2 a^2 / theta0^2) da on
+// [0, min(pi, 12 theta0)] (the integrand is below e^-288 beyond), 32 panels
+// of the 16-point Gauss rule: a panel spans at most 0.375 theta0, where the
+// rule is exact to rounding.  512 evaluations in place of a million of
+// Simpson's rule, whose rounding (4e-13) was the larger error.
 inline double F_gauss(double t0) {
-    const double b = std::fmin(M_PI, 12.0 * t0);
-    const int n = 1 << 20;
-    const double h = b / n;
-    auto f = [&](double a) { return std::sin(a) * std::exp(-2.0 * a * a / (t0 * t0)); };
-    double s = f(0.0) + f(b);
-    for (int i = 1; i < n; ++i) s += (i & 1 ? 4.0 : 2.0) * f(i * h);
-    return s * h / 3.0;
+    static const Gauss16 g;
+    const double b = std::fmin(M_PI, 12.0 * t0), h = 0.5 * b / 32;
+    double s = 0.0;
+    for (int q = 0; q < 32; ++q)
+        for (int i = 0; i < 16; ++i) {
+            const double a = (2 * q + 1 + g.x[i]) * h;
+            s += g.w[i] * std::sin(a) * std::exp(-2.0 * a * a / (t0 * t0));
+        }
+    return s * h;
 }
 
 inline tf_status validate_pulse(const tf_pulse* p) {
@@ -127,15 +185,50 @@ inline void spectral_table(const tf_pulse* p, std::vector<double>& tab, double& 
         tab.push_back(a);
         tab.push_back(phi);
     }
+    // sum_m a_m cos(q_m - w_m z) at z = +-j h from u = sum a cos q cos(w z) and
+    // v = sum a sin q sin(w z), cos and sin of w_m z carried from j to j + 1 by
+    // a rotation and evaluated anew every 32 (the rounding of 32 rotations,
+    // about 1e-15, is that of the phase w z itself): one cosine per 16 terms
+    // in place of one per term, which was most of tf_set_pulse's host time.
     const double h = p->wavelength / 128.0;
     const long jmax = (long)std::floor(0.5 * p->L / h);
-    gnorm = 0.0;
     const int K = (int)(tab.size() / 3);
-    for (long j = -jmax; j <= jmax; ++j) {
-        const double z = j * h;
-        double acc = 0.0;
-        for (int m = 0; m < K; ++m) acc += tab[3 * m + 1] * std::cos(p->cep + 0.5 * M_PI + tab[3 * m + 2] - tab[3 * m] * z);
-        gnorm = std::fmax(gnorm, std::fabs(acc));
+    std::vector<double> buf(6 * (size_t)K);
+    double *A = buf.data(), *B = A + K, *c = B + K, *s = c + K, *rc = s + K, *rs = rc + K;
+    for (int m = 0; m < K; ++m) {
+        const double q = p->cep + 0.5 * M_PI + tab[3 * m + 2];
+        A[m] = tab[3 * m + 1] * std::cos(q);
+        B[m] = tab[3 * m + 1] * std::sin(q);
+        rc[m] = std::cos(tab[3 * m] * h);
+        rs[m] = std::sin(tab[3 * m] * h);
+    }
+    gnorm = 0.0;
+    for (long j = 0; j <= jmax; ++j) {
+        if (j % 32 == 0)
+            for (int m = 0; m < K; ++m) {
+                c[m] = std::cos(tab[3 * m] * (j * h));
+                s[m] = std::sin(tab[3 * m] * (j * h));
+            }
+        // four partial sums each, so that neither the rotations nor the sums wait on one another
+        double u[4] = {0.0, 0.0, 0.0, 0.0}, v[4] = {0.0, 0.0, 0.0, 0.0};
+        int m = 0;
+        for (; m + 4 <= K; m += 4)
+            for (int k = 0; k < 4; ++k) {
+                const double cm = c[m + k], sm = s[m + k];
+                u[k] += A[m + k] * cm;
+                v[k] += B[m + k] * sm;
+                c[m + k] = cm * rc[m + k] - sm * rs[m + k];
+                s[m + k] = sm * rc[m + k] + cm * rs[m + k];
+            }
+        for (; m < K; ++m) {
+            const double cm = c[m], sm = s[m];
+            u[0] += A[m] * cm;
+            v[0] += B[m] * sm;
+            c[m] = cm * rc[m] - sm * rs[m];
+            s[m] = sm * rc[m] + cm * rs[m];
+        }
+        const double us = (u[0] + u[1]) + (u[2] + u[3]), vs = (v[0] + v[1]) + (v[2] + v[3]);
+        gnorm = std::fmax(gnorm, std::fmax(std::fabs(us + vs), std::fabs(us - vs)));
     }
 }
 
@@ -217,23 +310,16 @@ inline int pulse_npoly(const tf_pulse* pulse, const std::vector<double>& all, in
     return spec_poly_count(pulse->L, all[0] + all[1] * (nfreq - 1));
 }
 
-// Doubles of a pulse's device tables: the interval polynomials (first, for
-// their alignment), then pulse_tables' output.
-inline size_t pulse_table_doubles(const std::vector<double>& all, int npoly) {
-    return (size_t)npoly * 2 * SPEC_COEF + all.size();
-}
-
 // Points the descriptor at the pulse's device tables: npoly interval
-// polynomials (filled by the caller with launch_spec_poly), then a copy of
-// pulse_tables' output.
-inline void pulse_dev_tables(PulseDev& p, const tf_pulse* pulse, const double* dev, size_t spec_len, double gnorm,
-                             int nfreq, int npoly) {
-    const double* tab = dev + (size_t)npoly * 2 * SPEC_COEF;
+// polynomials (16-byte aligned; filled by the caller with launch_spec_poly)
+// and a copy of pulse_tables' output.
+inline void pulse_dev_tables(PulseDev& p, const tf_pulse* pulse, const double* poly, const double* tab, size_t spec_len,
+                             double gnorm, int nfreq, int npoly) {
     if (pulse->envelope == TF_ENV_SPECTRAL) {
         p.spec = tab;
         p.nfreq = nfreq;
         p.gnorm = gnorm;
-        p.poly = dev;
+        p.poly = poly;
         p.npoly = npoly;
         p.poly_inv = npoly / pulse->L;
     }

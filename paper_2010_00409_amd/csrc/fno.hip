@@ -1434,6 +1434,7 @@ tf_status tf_fno_create(int32_t max_batch, int32_t training, int32_t nbasis, voi
     *out = nullptr;
     if (max_batch < 1 || max_batch > 128) return fail(TF_EINVAL, "max_batch must be in [1, 128]");
     if (nbasis != 1 && nbasis != 2 && nbasis != 4) return fail(TF_EINVAL, "nbasis must be 1, 2 or 4");
+    tf::host::BlockCache::get().clear();      // blocks kept from finished solvers and batches
     std::unique_ptr<tf_fno> f(new tf_fno());
     f->nb = nbasis;
     f->np = nparams(nbasis);

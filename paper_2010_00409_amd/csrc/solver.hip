@@ -24,6 +24,85 @@ std::string& tf::host::last_error() {
     return e;
 }
 
+namespace tf {
+namespace host {
+
+BlockCache& BlockCache::get() {
+    static BlockCache* c = new BlockCache();      // lives until the process ends
+    return *c;
+}
+
+constexpr size_t CACHE_MIN_BLOCK = size_t(32) << 20;
+
+void BlockCache::clear_locked() {
+    for (const Block& b : free_) (void)hipFree(b.ptr);
+    free_.clear();
+}
+
+void BlockCache::clear() {
+    std::lock_guard<std::mutex> lk(mu_);
+    clear_locked();
+}
+
+hipError_t BlockCache::take(void** ptr, size_t bytes, size_t* got) {
+    *got = bytes;
+    if (bytes < CACHE_MIN_BLOCK) return hipMalloc(ptr, bytes);
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lk(mu_);
+    // the smallest block that holds the request with at most a quarter to spare
+    size_t best = free_.size();
+    for (size_t i = 0; i < free_.size(); ++i)
+        if (free_[i].dev == dev && free_[i].bytes >= bytes && free_[i].bytes <= bytes + bytes / 4 &&
+            (best == free_.size() || free_[i].bytes < free_[best].bytes))
+            best = i;
+    if (best < free_.size()) {
+        *ptr = free_[best].ptr;
+        *got = free_[best].bytes;
+        free_.erase(free_.begin() + (long)best);
+        return hipSuccess;
+    }
+    for (size_t i = 0; i < free_.size();) {
+        if (++free_[i].passed > 4) {
+            (void)hipFree(free_[i].ptr);
+            free_.erase(free_.begin() + (long)i);
+        } else {
+            ++i;
+        }
+    }
+    e = hipMalloc(ptr, bytes);
+    if (e == hipErrorOutOfMemory && !free_.empty()) {
+        (void)hipGetLastError();
+        clear_locked();
+        e = hipMalloc(ptr, bytes);
+    }
+    return e;
+}
+
+void BlockCache::put(void* ptr, size_t bytes) {
+    if (!ptr) return;
+    int dev = 0;
+    size_t avail = 0, total = 0;
+    if (bytes < CACHE_MIN_BLOCK || hipGetDevice(&dev) != hipSuccess || hipDeviceSynchronize() != hipSuccess ||
+        hipMemGetInfo(&avail, &total) != hipSuccess || bytes > total / 8) {
+        (void)hipFree(ptr);
+        return;
+    }
+    std::lock_guard<std::mutex> lk(mu_);
+    size_t held = bytes;
+    for (const Block& b : free_) held += b.bytes;
+    while (held > total / 8 && !free_.empty()) {          // the oldest first
+        held -= free_.front().bytes;
+        (void)hipFree(free_.front().ptr);
+        free_.erase(free_.begin());
+    }
+    free_.push_back({dev, ptr, bytes, 0});
+}
+
+}  // namespace host
+}  // namespace tf
+
 struct tf_solver {
     tf_grid grid{};
     int prec = TF_F32;
@@ -31,14 +110,20 @@ struct tf_solver {
     hipStream_t stream = nullptr;
     long cells = 0;
     int nkx = 0;
-    void* state = nullptr;
+    void* state = nullptr;         // state and spec: blocks of the cache, with their sizes
     void* spec = nullptr;
+    size_t state_bytes = 0, spec_bytes = 0;
     void* tw[3] = {nullptr, nullptr, nullptr};
     double* partials = nullptr;
     size_t npartials = 0;
     double* results = nullptr;     // 8 doubles
     void* pulse_tab = nullptr;     // device tables of the last pulse, kept for the next
     size_t pulse_tab_len = 0;      // its size in doubles
+    // pinned copy of the uploaded part and the event after its upload: the
+    // call does not wait for the stream
+    void* pulse_host = nullptr;
+    size_t pulse_host_len = 0;
+    hipEvent_t pulse_up = nullptr;
     void* dcbuf = nullptr;         // diagnostics: packed kx = 0 slot after the forward z FFT
     tf::RowMap rm{};
     bool fast = true;              // use the specialised float32 column kernels
@@ -203,9 +288,16 @@ void free_all(tf_solver* s) {
     if (s->cap) (void)hipStreamDestroy(s->cap);
     s->step_exec = nullptr;
     s->cap = nullptr;
+    if (s->pulse_up) (void)hipEventDestroy(s->pulse_up);
+    if (s->pulse_host) (void)hipHostFree(s->pulse_host);
+    s->pulse_up = nullptr;
+    s->pulse_host = nullptr;
     for (hipEvent_t ev : s->evpool) (void)hipEventDestroy(ev);
     s->evpool.clear();
-    void* ptrs[] = {s->state, s->spec, s->tw[0], s->tw[1], s->tw[2], s->partials, s->results,
+    BlockCache::get().put(s->state, s->state_bytes);
+    BlockCache::get().put(s->spec, s->spec_bytes);
+    s->state = s->spec = nullptr;
+    void* ptrs[] = {s->tw[0], s->tw[1], s->tw[2], s->partials, s->results,
                     s->pulse_tab, s->dcbuf, s->scratch_out, s->jstate, s->jspec};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -382,15 +474,15 @@ tf_status tf_create(const tf_grid* grid, int32_t precision, void* hip_stream, tf
         delete s;
         return fail(TF_ENOMEM, "solver needs " + std::to_string(need) + " device bytes, above TFOCUS_MAX_DEVICE_BYTES");
     }
-    auto alloc = [&](void** p, size_t b) -> tf_status {
-        hipError_t e = hipMalloc(p, b);
+    auto alloc = [&](void** p, size_t b, size_t* got = nullptr) -> tf_status {
+        hipError_t e = got ? BlockCache::get().take(p, b, got) : hipMalloc(p, b);
         if (e == hipErrorOutOfMemory) return fail(TF_ENOMEM, "hipMalloc of " + std::to_string(b) + " bytes failed");
         if (e != hipSuccess) return fail(TF_EDEVICE, std::string("hipMalloc: ") + hipGetErrorString(e));
         return TF_OK;
     };
     tf_status st = TF_OK;
-    if (st == TF_OK) st = alloc(&s->state, state_b);
-    if (st == TF_OK) st = alloc(&s->spec, spec_b);
+    if (st == TF_OK) st = alloc(&s->state, state_b, &s->state_bytes);
+    if (st == TF_OK) st = alloc(&s->spec, spec_b, &s->spec_bytes);
     const int ns[3] = {grid->nx, grid->ny, grid->nz};
     for (int a = 0; a < 3 && st == TF_OK; ++a) st = alloc(&s->tw[a], 2 * s->esize * ns[a]);
     if (st == TF_OK) st = alloc((void**)&s->partials, s->npartials * sizeof(double));
@@ -470,21 +562,27 @@ tf_status tf_set_pulse(tf_solver* s, const tf_pulse* pulse, tf_pulse_info* info)
     if (st != TF_OK) return st;
     if (!all.empty()) {
         const int npoly = pulse_npoly(pulse, all, nfreq);
-        const size_t len = pulse_table_doubles(all, npoly), poly_len = len - all.size();
-        if (s->pulse_tab_len < len) {
-            if (s->pulse_tab) {
-                TF_HIP(hipStreamSynchronize(s->stream));
-                TF_HIP(hipFree(s->pulse_tab));
-                s->pulse_tab = nullptr;
-                s->pulse_tab_len = 0;
-            }
+        const size_t poly_len = (size_t)npoly * 2 * tf::SPEC_COEF, len = poly_len + all.size();
+        if (s->pulse_tab_len < len || s->pulse_host_len < all.size()) {
+            TF_HIP(hipStreamSynchronize(s->stream));
+            if (s->pulse_tab) (void)hipFree(s->pulse_tab);
+            if (s->pulse_host) (void)hipHostFree(s->pulse_host);
+            s->pulse_tab = s->pulse_host = nullptr;
+            s->pulse_tab_len = s->pulse_host_len = 0;
             TF_HIP(hipMalloc(&s->pulse_tab, len * sizeof(double)));
             s->pulse_tab_len = len;
+            TF_HIP(hipHostMalloc(&s->pulse_host, all.size() * sizeof(double)));
+            s->pulse_host_len = all.size();
+            if (!s->pulse_up) TF_HIP(hipEventCreateWithFlags(&s->pulse_up, hipEventDisableTiming));
+        } else {
+            TF_HIP(hipEventSynchronize(s->pulse_up));     // the last upload has left the staging buffer
         }
         double* dev = static_cast<double*>(s->pulse_tab);
-        TF_HIP(hipMemcpyAsync(dev + poly_len, all.data(), all.size() * sizeof(double), hipMemcpyHostToDevice, s->stream));
-        TF_HIP(hipStreamSynchronize(s->stream));
-        pulse_dev_tables(p, pulse, dev, spec_len, gnorm, nfreq, npoly);
+        std::memcpy(s->pulse_host, all.data(), all.size() * sizeof(double));
+        TF_HIP(hipMemcpyAsync(dev + poly_len, s->pulse_host, all.size() * sizeof(double), hipMemcpyHostToDevice,
+                              s->stream));
+        TF_HIP(hipEventRecord(s->pulse_up, s->stream));
+        pulse_dev_tables(p, pulse, dev, dev + poly_len, spec_len, gnorm, nfreq, npoly);
         if (npoly > 0) TF_HIP(tf::launch_spec_poly(dev, p, s->stream));
     }
     tf::GridDev gd = grid_dev(s->grid);
