@@ -340,7 +340,8 @@ tf_status tf_batch_destroy(tf_batch* b);
 /* ---- kernel plans and the autotuner ------------------------------------ */
 
 /* Plan file consulted by tf_create and tf_batch_create (also taken from the
- * environment variable TFOCUS_PLAN_FILE).  NULL or "" clears it. */
+ * environment variable TFOCUS_PLAN_FILE).  NULL or "" clears it.  A line with
+ * nx = ny = 0 holds for every grid of its nz without a line of its own. */
 tf_status tf_set_plan_file(const char* path);
 
 /* Host only.  The kernel plan tf_create and tf_batch_create use for a grid:

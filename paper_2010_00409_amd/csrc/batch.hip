@@ -53,7 +53,8 @@ std::string device_arch() {
 
 // Plan file: '#' comments; entries
 // "arch prec nx ny nz row_block fast zvariant ystrip ms" (lines without the
-// ystrip field keep 64-column y strips).  False for comments and bad lines.
+// ystrip field keep 64-column y strips); nx = ny = 0 stands for every grid of
+// that nz that has no line of its own.  False for comments and bad lines.
 bool parse_plan_line(const std::string& line, PlanKey& k, KernelPlan& p, double& ms) {
     if (line.empty() || line[0] == '#') return false;
     std::istringstream is(line);
@@ -120,8 +121,12 @@ tf::host::KernelPlan tf::host::plan_for(const tf_grid& g, int precision) {
         }
         if (!g_plan_path.empty()) {
             load_plans_locked();
-            const PlanKey k{device_arch(), precision, g.nx, g.ny, g.nz};
+            PlanKey k{device_arch(), precision, g.nx, g.ny, g.nz};
             auto it = g_plans.find(k);
+            if (it == g_plans.end()) {
+                k.nx = k.ny = 0;
+                it = g_plans.find(k);
+            }
             if (it != g_plans.end() && tf::row_block_ok(it->second.row_block, g.ny)) p = it->second;
         }
     }
