@@ -209,11 +209,13 @@ tf_status tf_set_cutout(tf_solver* s, double R_min, double R_max);
  * per-mode rotation of Eqs. (3)-(4) with C = cos(c|k|dt), S = sin(c|k|dt),
  * inverse FFT.  k-space conventions: forward transform exp(-i k.x); k_hat =
  * 0 at k = 0; Nyquist indices contribute 0 to k.  t += nsteps * dt.
- * Asynchronous on the solver's stream.  Runs of eight steps are replayed
- * from a graph captured on a private stream at the first such call with
- * this dt (and again when dt changes), owned by the solver; the first step
- * after tf_set_pulse, the remainder and all steps while tf_profile is on
- * are launched directly.  Both give the same bits. */
+ * Asynchronous on the solver's stream.  Within one call the field between two
+ * steps, which nothing can read, is not written to memory.  After the call's
+ * first step, groups of eight are replayed from a graph captured on a private
+ * stream at the first such call with this dt (and again when dt changes),
+ * owned by the solver; the first step, the remainder and all steps while
+ * tf_profile is on are launched directly.  All give the bits of single
+ * steps. */
 tf_status tf_advance(tf_solver* s, int64_t nsteps, double dt);
 
 /* One step of dt with a current density j held over the step (Sec. II.A,
@@ -290,7 +292,9 @@ tf_status tf_get_grid(const tf_solver* s, tf_grid* grid);
 tf_status tf_advance_noalloc(const tf_grid* grid, int32_t precision, void* state_dev, int64_t nsteps, double dt,
                              int32_t project_b_first, void* hip_stream);
 
-/* Pass kinds reported by tf_profile_read. */
+/* Pass kinds reported by tf_profile_read.  Between the steps of a run one
+ * launch takes the inverse x pass of a step and the forward one of the next;
+ * it counts as TF_PASS_X_INVERSE. */
 typedef enum {
     TF_PASS_X_FORWARD = 0, TF_PASS_Y_FORWARD = 1, TF_PASS_Z_STEP = 2, TF_PASS_Y_INVERSE = 3,
     TF_PASS_X_INVERSE = 4, TF_PASS_INIT = 5, TF_PASS_READOUT = 6, TF_PASS_OTHER = 7,

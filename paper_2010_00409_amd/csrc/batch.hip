@@ -225,15 +225,33 @@ hipError_t enqueue_group(tf_batch* b, Group& G, const int64_t* nsteps, const dou
         e = tf::launch_init_map<T>(static_cast<T*>(G.state) + s * G.state_elems, gd, b->pdev[i], G.stream);
     }
     const int64_t kmax = nslot ? nsteps[G.slot_of[0]] : 0;
+    // slots with a step k are the prefix [0, active(k)): longest runs first
+    auto active = [&](int64_t k) {
+        int m = 0;
+        while (m < nslot && nsteps[G.slot_of[m]] > k) ++m;
+        return m;
+    };
+    tf::Batch bt;
+    bt.sreal = (long)G.state_elems;
+    bt.sspec = (long)(G.spec_elems / 2);
+    bt.cdt = G.cdt;
+    T* const state = static_cast<T*>(G.state);
+    T* const spec = static_cast<T*>(G.spec);
+    bt.n = kmax > 0 ? active(0) : 0;
+    if (e == hipSuccess && bt.n > 0)
+        e = tf::launch_x_forward<T>(state, spec, G.tw[0], G.grid.nx, G.grid.ny, G.grid.nz, G.rm, bt, G.stream);
     for (int64_t k = 0; k < kmax && e == hipSuccess; ++k) {
-        int active = 0;
-        while (active < nslot && nsteps[G.slot_of[active]] > k) ++active;
-        tf::Batch bt;
-        bt.n = active;
-        bt.sreal = (long)G.state_elems;
-        bt.sspec = (long)(G.spec_elems / 2);
-        bt.cdt = G.cdt;
-        e = step_passes<T>(G.state, G.spec, G.tw, G.grid, G.rm, G.kp, 0.0, k == 0, bt, G.stream);
+        e = step_core<T>(spec, G.tw, G.grid, G.rm, G.kp, 0.0, k == 0, k == 0, bt, G.stream);
+        // slots that go on take the x pair pass, the others end their run
+        const int now = bt.n, next = active(k + 1);
+        if (e == hipSuccess && next < now) {
+            bt.n = now - next;
+            e = tf::launch_x_inverse<T>(spec + next * G.spec_elems, state + next * G.state_elems, G.tw[0], G.grid.nx,
+                                        G.grid.ny, G.grid.nz, G.rm, bt, G.stream);
+        }
+        bt.n = next;
+        if (e == hipSuccess && next > 0)
+            e = tf::launch_x_pair<T>(spec, G.tw[0], G.grid.nx, G.grid.ny, G.grid.nz, G.rm, bt, G.stream);
     }
     for (int s = 0; s < nslot && e == hipSuccess; ++s) {
         const int i = G.slot_of[s];

@@ -441,21 +441,31 @@ inline bool fast_offsets_fit(const tf_grid& g, int row_block, int precision) {
     return z_fast_offsets_fit(g.nx, g.nz, row_block, cb);
 }
 
-// Pass sequence of one step on a set of same-shape instances.
+// The passes of a run of steps on a set of same-shape instances: the x
+// forward pass of the first step, then per step the y forward, z and y
+// inverse passes (step_core), and between two steps the x pair pass in place
+// of the inverse and the forward one; the x inverse pass ends the run.
 template <typename T>
-hipError_t step_passes(void* state, void* spec, void* const* tw, const tf_grid& g, const RowMap& rm,
-                       const KernelPlan& kp, double dt, bool project_b, Batch bt, hipStream_t st) {
-    hipError_t e = launch_x_forward<T>(static_cast<const T*>(state), spec, tw[0], g.nx, g.ny, g.nz, rm, bt, st);
-    if (e != hipSuccess) return e;
-    e = launch_y_pass<T>(spec, tw[1], g.nx, g.ny, g.nz, -1, rm, kp.yarg(), bt, st);
+hipError_t step_core(void* spec, void* const* tw, const tf_grid& g, const RowMap& rm, const KernelPlan& kp, double dt,
+                     bool project_b, bool first, Batch bt, hipStream_t st) {
+    hipError_t e = launch_y_pass<T>(spec, tw[1], g.nx, g.ny, g.nz, first ? Y_FORWARD : Y_FORWARD_PAIR, rm, kp.yarg(), bt,
+                                    st);
     if (e != hipSuccess) return e;
     StepParams p = step_params(g, dt, project_b, kp.zvariant);
     if (bt.cdt) p.phase32 = 0;          // per-instance time steps: the phase bound is not known here
     e = launch_z_pass<T>(spec, tw[2], p, rm, Z_STEP, nullptr, nullptr, nullptr, kp.fast, bt, st);
     if (e != hipSuccess) return e;
-    e = launch_y_pass<T>(spec, tw[1], g.nx, g.ny, g.nz, +1, rm, kp.yarg(), bt, st);
-    if (e != hipSuccess) return e;
-    return launch_x_inverse<T>(spec, static_cast<T*>(state), tw[0], g.nx, g.ny, g.nz, rm, bt, st);
+    return launch_y_pass<T>(spec, tw[1], g.nx, g.ny, g.nz, Y_INVERSE, rm, kp.yarg(), bt, st);
+}
+
+// One step on its own.
+template <typename T>
+hipError_t step_passes(void* state, void* spec, void* const* tw, const tf_grid& g, const RowMap& rm,
+                       const KernelPlan& kp, double dt, bool project_b, Batch bt, hipStream_t st) {
+    hipError_t e = launch_x_forward<T>(static_cast<const T*>(state), spec, tw[0], g.nx, g.ny, g.nz, rm, bt, st);
+    if (e == hipSuccess) e = step_core<T>(spec, tw, g, rm, kp, dt, project_b, true, bt, st);
+    if (e == hipSuccess) e = launch_x_inverse<T>(spec, static_cast<T*>(state), tw[0], g.nx, g.ny, g.nz, rm, bt, st);
+    return e;
 }
 
 }  // namespace host

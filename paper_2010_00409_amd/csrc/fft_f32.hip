@@ -9,7 +9,8 @@ extern template __global__ void k_z_wave256<4, 3>(float2* __restrict__, const fl
                                                   Batch);
 template hipError_t launch_x_forward<float>(const float*, void*, const void*, int, int, int, RowMap, Batch, hipStream_t);
 template hipError_t launch_x_inverse<float>(const void*, float*, const void*, int, int, int, RowMap, Batch, hipStream_t);
-template hipError_t launch_y_pass<float>(void*, const void*, int, int, int, int, RowMap, int, Batch, hipStream_t);
+template hipError_t launch_x_pair<float>(void*, const void*, int, int, int, RowMap, Batch, hipStream_t);
+template hipError_t launch_y_pass<float>(void*, const void*, int, int, int, YOrder, RowMap, int, Batch, hipStream_t);
 template hipError_t launch_z_pass<float>(void*, const void*, const StepParams&, RowMap, int, double*, void*, int*, bool,
                                        Batch, hipStream_t);
 template int z_diag_blocks<float>(int, int, int);

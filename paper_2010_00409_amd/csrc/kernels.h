@@ -76,11 +76,21 @@ template <typename T> hipError_t launch_x_forward(const T* real, void* spec, con
 // Inverse x pass: spectral -> real state.
 template <typename T> hipError_t launch_x_inverse(const void* spec, T* real, const void* tw,
                                                   int nx, int ny, int nz, RowMap rm, Batch bt, hipStream_t st);
-// In-place y transform of the spectral array, dir = -1 forward, +1 inverse.
-// ystrip: columns per strip of the fast float32 kernel (64 or 32; 64 falls
-// back to 32 on rows of 32 (mod 64) slots); 0 forces the generic kernels.
+// Inverse x pass of one step and forward x pass of the next in one, in place
+// on the spectral array; the field between them is not written.
+template <typename T> hipError_t launch_x_pair(void* spec, const void* tw, int nx, int ny, int nz, RowMap rm,
+                                               Batch bt, hipStream_t st);
+// In-place y transform of the spectral array.  The order of the z planes
+// follows the pass before: the x forward pass ends on the last rows
+// (Y_FORWARD takes the planes from the last to the first), the x pair pass on
+// the first (Y_FORWARD_PAIR: first to last); the inverse follows the z pass,
+// a transpose that no order suits (first to last).
+// ystrip: columns per strip of the tuned float32 kernels (64 or 32; 64 falls
+// back to 32 on rows that are not a multiple of 64 slots); 0 forces the
+// generic kernels.
+enum YOrder { Y_FORWARD, Y_FORWARD_PAIR, Y_INVERSE };
 template <typename T> hipError_t launch_y_pass(void* spec, const void* tw, int nx, int ny, int nz,
-                                               int dir, RowMap rm, int ystrip, Batch bt, hipStream_t st);
+                                               YOrder order, RowMap rm, int ystrip, Batch bt, hipStream_t st);
 // z pass: Z_STEP = forward z FFT, Eqs. (3)-(4) update, inverse z FFT, in place;
 // Z_DIAG = forward z FFT and per-block maxima |k.E|, |k.B|, |E|, |B| into
 // partials (4 doubles per block; the packed kx = 0 slot goes through dc, a

@@ -143,8 +143,8 @@ struct tf_solver {
     bool prof = false;
     std::vector<hipEvent_t> evpool;
     std::vector<int> rec_kind;
-    // GRAPH_STEPS steps of one dt, captured once on a private stream and
-    // replayed on `stream` by tf_advance
+    // GRAPH_STEPS steps of a run after its first, of one dt, captured once on a
+    // private stream and replayed on `stream` by tf_advance
     hipStream_t cap = nullptr;
     hipGraphExec_t step_exec = nullptr;
     double step_dt = 0.0;
@@ -181,7 +181,7 @@ hipError_t forward_xy(tf_solver* s, int kind_x, int kind_y) {
     });
     if (e != hipSuccess) return e;
     return timed(s, kind_y, [&] {
-        return tf::launch_y_pass<T>(s->spec, s->tw[1], g.nx, g.ny, g.nz, -1, s->rm, s->fast ? s->ystrip : 0,
+        return tf::launch_y_pass<T>(s->spec, s->tw[1], g.nx, g.ny, g.nz, tf::Y_FORWARD, s->rm, s->fast ? s->ystrip : 0,
                                     tf::Batch{}, s->stream);
     });
 }
@@ -199,7 +199,7 @@ hipError_t current_step(tf_solver* s, double dt, bool project_b) {
     });
     if (e != hipSuccess) return e;
     e = timed(s, TF_PASS_OTHER, [&] {
-        return tf::launch_y_pass<T>(s->jspec, s->tw[1], g.nx, g.ny, g.nz, -1, s->rm, ys, tf::Batch{}, s->stream);
+        return tf::launch_y_pass<T>(s->jspec, s->tw[1], g.nx, g.ny, g.nz, tf::Y_FORWARD, s->rm, ys, tf::Batch{}, s->stream);
     });
     if (e != hipSuccess) return e;
     e = forward_xy<T>(s, TF_PASS_X_FORWARD, TF_PASS_Y_FORWARD);
@@ -210,7 +210,7 @@ hipError_t current_step(tf_solver* s, double dt, bool project_b) {
     });
     if (e != hipSuccess) return e;
     e = timed(s, TF_PASS_Y_INVERSE, [&] {
-        return tf::launch_y_pass<T>(s->spec, s->tw[1], g.nx, g.ny, g.nz, +1, s->rm, ys, tf::Batch{}, s->stream);
+        return tf::launch_y_pass<T>(s->spec, s->tw[1], g.nx, g.ny, g.nz, tf::Y_INVERSE, s->rm, ys, tf::Batch{}, s->stream);
     });
     if (e != hipSuccess) return e;
     return timed(s, TF_PASS_X_INVERSE, [&] {
@@ -219,13 +219,17 @@ hipError_t current_step(tf_solver* s, double dt, bool project_b) {
     });
 }
 
-// One step; with diag_blocks the z pass is the generic kernel that also
-// writes the diagnostics of the new state into s->partials (Z_STEP_DIAG),
-// and *diag_blocks receives its count of 4-wide partials.
+// y forward, z and y inverse passes of one step; with diag_blocks the z pass is
+// the generic kernel that also writes the diagnostics of the new state into
+// s->partials (Z_STEP_DIAG), and *diag_blocks receives its count of 4-wide
+// partials.
 template <typename T>
-hipError_t one_step(tf_solver* s, double dt, bool project_b, int* diag_blocks = nullptr) {
+hipError_t core_passes(tf_solver* s, double dt, bool project_b, tf::YOrder order, int* diag_blocks = nullptr) {
     const tf_grid& g = s->grid;
-    hipError_t e = forward_xy<T>(s, TF_PASS_X_FORWARD, TF_PASS_Y_FORWARD);
+    const int ys = s->fast ? s->ystrip : 0;
+    hipError_t e = timed(s, TF_PASS_Y_FORWARD, [&] {
+        return tf::launch_y_pass<T>(s->spec, s->tw[1], g.nx, g.ny, g.nz, order, s->rm, ys, tf::Batch{}, s->stream);
+    });
     if (e != hipSuccess) return e;
     tf::StepParams p = step_params(s->grid, dt, project_b, s->zvariant);
     e = timed(s, TF_PASS_Z_STEP, [&] {
@@ -236,23 +240,43 @@ hipError_t one_step(tf_solver* s, double dt, bool project_b, int* diag_blocks = 
                                     tf::Batch{}, s->stream);
     });
     if (e != hipSuccess) return e;
-    e = timed(s, TF_PASS_Y_INVERSE, [&] {
-        return tf::launch_y_pass<T>(s->spec, s->tw[1], g.nx, g.ny, g.nz, +1, s->rm, s->fast ? s->ystrip : 0,
-                                    tf::Batch{}, s->stream);
+    return timed(s, TF_PASS_Y_INVERSE, [&] {
+        return tf::launch_y_pass<T>(s->spec, s->tw[1], g.nx, g.ny, g.nz, tf::Y_INVERSE, s->rm, ys, tf::Batch{}, s->stream);
     });
-    if (e != hipSuccess) return e;
+}
+
+template <typename T> hipError_t x_in(tf_solver* s) {
+    const tf_grid& g = s->grid;
+    return timed(s, TF_PASS_X_FORWARD, [&] {
+        return tf::launch_x_forward<T>(static_cast<const T*>(s->state), s->spec, s->tw[0], g.nx, g.ny, g.nz, s->rm,
+                                       tf::Batch{}, s->stream);
+    });
+}
+
+template <typename T> hipError_t x_out(tf_solver* s) {
+    const tf_grid& g = s->grid;
     return timed(s, TF_PASS_X_INVERSE, [&] {
         return tf::launch_x_inverse<T>(s->spec, static_cast<T*>(s->state), s->tw[0], g.nx, g.ny, g.nz, s->rm,
                                        tf::Batch{}, s->stream);
     });
 }
 
-// Steps per captured graph: the launch cost of the remaining steps is one
-// graph launch per GRAPH_STEPS steps.
+// One more step of a run: the x pair pass, then the step's own passes.
+template <typename T>
+hipError_t next_step(tf_solver* s, double dt) {
+    const tf_grid& g = s->grid;
+    hipError_t e = timed(s, TF_PASS_X_INVERSE, [&] {
+        return tf::launch_x_pair<T>(s->spec, s->tw[0], g.nx, g.ny, g.nz, s->rm, tf::Batch{}, s->stream);
+    });
+    return e == hipSuccess ? core_passes<T>(s, dt, false, tf::Y_FORWARD_PAIR) : e;
+}
+
+// Steps per captured graph: the launch cost of the steps after a run's first
+// is one graph launch per GRAPH_STEPS steps.
 constexpr int64_t GRAPH_STEPS = 8;
 
-// The graph of GRAPH_STEPS steps of dt (without the B projection), captured
-// on first use and again whenever dt changes.
+// The graph of GRAPH_STEPS further steps of dt, captured on first use and
+// again whenever dt changes.
 template <typename T>
 tf_status step_graph(tf_solver* s, double dt) {
     if (s->step_exec && std::memcmp(&s->step_dt, &dt, sizeof dt) == 0) return TF_OK;
@@ -266,7 +290,7 @@ tf_status step_graph(tf_solver* s, double dt) {
     hipStream_t user = s->stream;
     s->stream = s->cap;                       // the pass launchers enqueue on s->stream
     hipError_t e = hipSuccess;
-    for (int64_t k = 0; k < GRAPH_STEPS && e == hipSuccess; ++k) e = one_step<T>(s, dt, false);
+    for (int64_t k = 0; k < GRAPH_STEPS && e == hipSuccess; ++k) e = next_step<T>(s, dt);
     s->stream = user;
     hipError_t e2 = hipStreamEndCapture(s->cap, &graph);
     if (e != hipSuccess || e2 != hipSuccess) {
@@ -280,6 +304,25 @@ tf_status step_graph(tf_solver* s, double dt) {
         return fail(TF_EDEVICE, std::string("step graph instantiate: ") + hipGetErrorString(e));
     }
     s->step_dt = dt;
+    return TF_OK;
+}
+
+// A run of nsteps >= 1 steps: the state is transformed along x once at its
+// start and once at its end.  The graph is made before anything is queued, so
+// that a failed capture leaves the state as it was.
+template <typename T>
+tf_status run_steps(tf_solver* s, int64_t nsteps, double dt, bool project_b) {
+    const int64_t graphs = s->prof ? 0 : (nsteps - 1) / GRAPH_STEPS;
+    if (graphs > 0) {
+        tf_status st = step_graph<T>(s, dt);
+        if (st != TF_OK) return st;
+    }
+    hipError_t e = x_in<T>(s);
+    if (e == hipSuccess) e = core_passes<T>(s, dt, project_b, tf::Y_FORWARD);
+    for (int64_t r = 0; r < graphs && e == hipSuccess; ++r) e = hipGraphLaunch(s->step_exec, s->stream);
+    for (int64_t i = 1 + graphs * GRAPH_STEPS; i < nsteps && e == hipSuccess; ++i) e = next_step<T>(s, dt);
+    if (e == hipSuccess) e = x_out<T>(s);
+    if (e != hipSuccess) return fail(TF_EDEVICE, std::string("step: ") + hipGetErrorString(e));
     return TF_OK;
 }
 
@@ -369,8 +412,15 @@ hipError_t noalloc_steps(const tf_grid& g, void* state, unsigned char* base, int
     void* tws[3] = {tw, tw + 2 * g.nx, tw + 2 * (g.nx + g.ny)};
     const KernelPlan kp = plan_for(g, precision);
     const tf::RowMap rm{g.ny, g.nz, kp.row_block};
-    for (int64_t k = 0; k < nsteps && e == hipSuccess; ++k)
-        e = step_passes<T>(state, spec, tws, g, rm, kp, dt, project_b_first && k == 0, tf::Batch{}, st);
+    if (nsteps == 0) return e;
+    e = tf::launch_x_forward<T>(static_cast<const T*>(state), spec, tws[0], g.nx, g.ny, g.nz, rm, tf::Batch{}, st);
+    for (int64_t k = 0; k < nsteps && e == hipSuccess; ++k) {
+        if (k > 0) e = tf::launch_x_pair<T>(spec, tws[0], g.nx, g.ny, g.nz, rm, tf::Batch{}, st);
+        if (e == hipSuccess)
+            e = step_core<T>(spec, tws, g, rm, kp, dt, project_b_first && k == 0, k == 0, tf::Batch{}, st);
+    }
+    if (e == hipSuccess)
+        e = tf::launch_x_inverse<T>(spec, static_cast<T*>(state), tws[0], g.nx, g.ny, g.nz, rm, tf::Batch{}, st);
     return e;
 }
 
@@ -613,29 +663,11 @@ tf_status tf_advance(tf_solver* s, int64_t nsteps, double dt) {
     if (!s) return fail(TF_EINVAL, "solver is NULL");
     if (nsteps < 0) return fail(TF_EINVAL, "nsteps must be >= 0");
     if (!std::isfinite(dt)) return fail(TF_EINVAL, "dt must be finite");
-    auto eager = [&](bool pb) -> tf_status {
-        hipError_t e = s->prec == TF_F64 ? one_step<double>(s, dt, pb) : one_step<float>(s, dt, pb);
-        if (e != hipSuccess) return fail(TF_EDEVICE, std::string("step: ") + hipGetErrorString(e));
-        return TF_OK;
-    };
-    int64_t i = 0;
-    if (s->project_b_next && nsteps > 0) {    // the first step after new fields also removes longitudinal B
-        tf_status st = eager(true);
+    if (nsteps > 0) {    // the first step after new fields also removes longitudinal B
+        const bool pb = s->project_b_next;
+        const tf_status st = s->prec == TF_F64 ? run_steps<double>(s, nsteps, dt, pb) : run_steps<float>(s, nsteps, dt, pb);
         if (st != TF_OK) return st;
         s->project_b_next = false;
-        i = 1;
-    }
-    // whole graphs of GRAPH_STEPS steps, unless every launch is being timed
-    const int64_t graphs = s->prof ? 0 : (nsteps - i) / GRAPH_STEPS;
-    if (graphs > 0) {
-        tf_status st = s->prec == TF_F64 ? step_graph<double>(s, dt) : step_graph<float>(s, dt);
-        if (st != TF_OK) return st;
-        for (int64_t r = 0; r < graphs; ++r) TF_HIP(hipGraphLaunch(s->step_exec, s->stream));
-        i += graphs * GRAPH_STEPS;
-    }
-    for (; i < nsteps; ++i) {
-        tf_status st = eager(false);
-        if (st != TF_OK) return st;
     }
     s->t = s->t + (double)nsteps * dt;
     return TF_OK;
@@ -770,7 +802,13 @@ tf_status tf_advance_diagnosed(tf_solver* s, int64_t nsteps, double dt, double* 
     }
     int nb = 0;
     const bool pb = s->project_b_next;
-    hipError_t e = s->prec == TF_F64 ? one_step<double>(s, dt, pb, &nb) : one_step<float>(s, dt, pb, &nb);
+    auto step = [&](auto zero) {
+        using T = decltype(zero);
+        hipError_t r = x_in<T>(s);
+        if (r == hipSuccess) r = core_passes<T>(s, dt, pb, tf::Y_FORWARD, &nb);
+        return r == hipSuccess ? x_out<T>(s) : r;
+    };
+    hipError_t e = s->prec == TF_F64 ? step(0.0) : step(0.0f);
     if (e != hipSuccess) return fail(TF_EDEVICE, std::string("diagnosed step: ") + hipGetErrorString(e));
     s->project_b_next = false;
     s->t = s->t + dt;
