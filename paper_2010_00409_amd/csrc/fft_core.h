@@ -137,8 +137,42 @@ template <typename T, int R, int DIR> __device__ __forceinline__ void dft_odd(C2
     }
 }
 
+template <typename T, int R, int DIR> __device__ __forceinline__ void dftR(C2<T>* v);
+
+// Length P Q for coprime P and Q without twiddles (Good's prime factor map):
+// with n = Q n1 + P n2 (mod P Q) and k = k1 (mod P), k2 (mod Q), n k / (P Q) is
+// n1 k1 / P + n2 k2 / Q up to an integer, so the transform is P x Q of the
+// shorter ones between two permutations, which are register names here.
+template <typename T, int P, int Q, int DIR> __device__ __forceinline__ void dft_coprime(C2<T>* v) {
+    constexpr int N = P * Q;
+    C2<T> a[P][Q];
+#pragma unroll
+    for (int n1 = 0; n1 < P; ++n1) {
+#pragma unroll
+        for (int n2 = 0; n2 < Q; ++n2) a[n1][n2] = v[(Q * n1 + P * n2) % N];
+        dftR<T, Q, DIR>(a[n1]);
+    }
+#pragma unroll
+    for (int k2 = 0; k2 < Q; ++k2) {
+        C2<T> b[P];
+#pragma unroll
+        for (int n1 = 0; n1 < P; ++n1) b[n1] = a[n1][k2];
+        dftR<T, P, DIR>(b);
+#pragma unroll
+        for (int k1 = 0; k1 < P; ++k1) {
+            int k = k2;                                      // the k below N with k = k1 (mod P), k2 (mod Q)
+            while (k % P != k1) k += Q;
+            v[k] = b[k1];
+        }
+    }
+}
+
 template <typename T, int R, int DIR> __device__ __forceinline__ void dftR(C2<T>* v) {
-    static_assert(R == 2 || R == 3 || R == 4 || R == 5 || R == 7 || R == 8, "radix 2, 3, 4, 5, 7 or 8");
+    static_assert(R == 2 || R == 3 || R == 4 || R == 5 || R == 7 || R == 8 || R == 20 || R == 24 || R == 28,
+                  "radix 2, 3, 4, 5, 7, 8, 20, 24 or 28");
+    if constexpr (R == 20) { dft_coprime<T, 5, 4, DIR>(v); return; }
+    if constexpr (R == 24) { dft_coprime<T, 3, 8, DIR>(v); return; }
+    if constexpr (R == 28) { dft_coprime<T, 7, 4, DIR>(v); return; }
     if constexpr (R == 2) dft2<T, DIR>(v);
     else if constexpr (R == 3) dft3<T, DIR>(v);
     else if constexpr (R == 4) dft4<T, DIR>(v);
@@ -237,24 +271,22 @@ __device__ __forceinline__ void fft_lds(C2<T>* buf, const C2<T>* tw, int tid) {
 // whose outputs land back in the cyclic layout in registers.  Radices must
 // divide E (each lane then runs E / R butterflies per stage).
 template <int N, int E> struct LGPlan {
-    static constexpr int a = log2_part(N);
-    static constexpr int b = log3_part(N);
-    static constexpr int c5 = logp_part(N, 5);
-    static constexpr int c7 = logp_part(N, 7);
+    // an odd factor (E = 20, 24 or 28) goes into the first stage, whose radix
+    // is then all of E; what is left is a power of two
+    static constexpr bool mixed = E == 20 || E == 24 || E == 28;
+    static constexpr int a = log2_part(mixed ? N / E : N);
     static constexpr int ea = log2_part(E);
-    // radix-8 stages if 8 | E, then 4s (if 4 | E) and 2s, then radix-3, 5, 7
+    // radix-8 stages if 8 | E, then 4s (if 4 | E) and 2s
     static constexpr int r8 = (ea >= 3) ? a / 3 : 0;
     static constexpr int rest = a - 3 * r8;              // remaining power of two
     static constexpr int n4 = (ea >= 2) ? rest / 2 : 0;
     static constexpr int n2 = rest - 2 * n4;
-    static constexpr int p2 = r8 + n4 + n2;
-    static constexpr int nst = p2 + b + c5 + c7;
+    static constexpr int m = mixed ? 1 : 0;
+    static constexpr int nst = m + r8 + n4 + n2;
     static constexpr int radix(int s) {
-        return s < r8 ? 8 : (s < r8 + n4 ? 4 : (s < p2 ? 2 : (s < p2 + b ? 3 : (s < p2 + b + c5 ? 5 : 7))));
+        return s < m ? E : (s < m + r8 ? 8 : (s < m + r8 + n4 ? 4 : 2));
     }
-    static_assert(b == 0 || E % 3 == 0, "radix-3 stages need 3 | E");
-    static_assert(c5 == 0 || E % 5 == 0, "radix-5 stages need 5 | E");
-    static_assert(c7 == 0 || E % 7 == 0, "radix-7 stages need 7 | E");
+    static_assert(N == (mixed ? E : 1) << a, "lane groups take 2^a, or 20, 24 or 28 times 2^a");
     static_assert(N % E == 0 && (N / E) <= 1024, "bad lane-group shape");
 };
 
