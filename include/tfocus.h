@@ -151,9 +151,8 @@ const char* tf_version(void);
 const char* tf_last_error(void);
 
 /* 1 if n is a supported axis length: 2^a (8 .. 1024), 3 2^a (24 .. 768),
- * 5 2^a (40 .. 640) or 7 2^a (56 .. 896).  Lengths with a factor 5 or 7
- * (the paper's 112 and 896 node axes, Sec. III.A) take radix-5 and radix-7
- * stages and run the generic y and z kernels. */
+ * 5 2^a (40 .. 640) or 7 2^a (56 .. 896, the paper's 112 and 896 node axes,
+ * Sec. III.A). */
 int32_t tf_supported_length(int32_t n);
 
 /* Host only.  Opening angle (Sec. II.B), amplitude (Eq. (9); Gaussian
@@ -231,9 +230,11 @@ tf_status tf_advance(tf_solver* s, int64_t nsteps, double dt);
  * tf_advance.  j: 3 nx ny nz elements of the solver's precision, layout
  * [component][z][y][x] (jx, jy, jz), x fastest, on the host (j_on_device =
  * 0; the call then waits for the copy) or on the solver's device (1),
- * borrowed for the call.  The first call allocates a six-component current
- * array and a second half spectrum (12 nx ny nz elements), kept until
- * tf_destroy.  t += dt.  Asynchronous on the solver's stream for device j.
+ * borrowed for the call.  The first call allocates the current's half spectrum
+ * (6 nx ny nz / 2 elements) and, for host or not 16-byte aligned j, a copy of
+ * the current (3 nx ny nz elements), kept until tf_destroy; the check against
+ * TFOCUS_MAX_DEVICE_BYTES counts 12 nx ny nz elements.  t += dt.  Asynchronous
+ * on the solver's stream for device j.
  * TF_EUNSUPPORTED where nine z columns do not fit the LDS (float64 with
  * nz = 1024); TF_ENOMEM above TFOCUS_MAX_DEVICE_BYTES. */
 tf_status tf_advance_current(tf_solver* s, const void* j, int32_t j_on_device, double dt);

@@ -14,7 +14,7 @@ template hipError_t launch_y_pass<float>(void*, const void*, int, int, int, YOrd
 template hipError_t launch_z_pass<float>(void*, const void*, const StepParams&, RowMap, int, double*, void*, int*, bool,
                                        Batch, hipStream_t);
 template int z_diag_blocks<float>(int, int, int);
-template hipError_t launch_z_current<float>(void*, const void*, const void*, const StepParams&, RowMap, hipStream_t);
+template hipError_t launch_z_current<float>(void*, const void*, const void*, const StepParams&, RowMap, bool, hipStream_t);
 template bool z_current_supported<float>(int);
 }  // namespace tf
 

@@ -105,11 +105,12 @@ template <typename T> hipError_t launch_z_pass(void* spec, const void* tw, const
                                                int* nblocks, bool fast, Batch bt, hipStream_t st);
 template <typename T> int z_diag_blocks(int nx, int ny, int nz);
 // z pass of a step with a current (Eqs. (1)-(2)): jspec holds the x- and
-// y-transformed current in components 0..2 of the same layout as spec.
-// Generic kernel, one mode slot per block, for every nz whose nine columns
-// fit the LDS (z_current_supported).
+// y-transformed current folded in z, component a of plane kz in component
+// 2 a + h of plane kz - h nz / 2, h = kz >= nz / 2 (rows of RowMap(ny, nz / 2,
+// G)).  fast: the register kernel where it serves nz; else, and for every nz
+// whose nine columns fit the LDS (z_current_supported), the generic one.
 template <typename T> hipError_t launch_z_current(void* spec, const void* jspec, const void* tw,
-                                                  const StepParams& p, RowMap rm, hipStream_t st);
+                                                  const StepParams& p, RowMap rm, bool fast, hipStream_t st);
 template <typename T> bool z_current_supported(int nz);
 
 // Twiddle tables are per axis length: tw[e] = exp(-2 pi i e / n).

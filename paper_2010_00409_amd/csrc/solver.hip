@@ -131,8 +131,8 @@ struct tf_solver {
     int zvariant = 0;
     void* scratch_out = nullptr;
     size_t scratch_bytes = 0;
-    // current steps (tf_advance_current): the current in components 0..2 of
-    // a six-component real array (3..5 stay zero) and its half spectrum
+    // current steps (tf_advance_current): the current where it has to be
+    // copied, and its half spectrum
     void* jstate = nullptr;
     void* jspec = nullptr;
     double t = 0.0;
@@ -186,27 +186,30 @@ hipError_t forward_xy(tf_solver* s, int kind_x, int kind_y) {
     });
 }
 
-// One step of Eqs. (1)-(2) with the current in s->jstate: the current and
-// the fields are x- and y-transformed, the z pass applies the update, and
-// the fields go back as in a vacuum step.
+// One step of Eqs. (1)-(2) with the current at j (device memory): the current,
+// folded in z into six components on nz / 2 planes (which is how its three
+// components already lie), and the fields are x- and y-transformed, the z pass
+// applies the update, and the fields go back as in a vacuum step.
 template <typename T>
-hipError_t current_step(tf_solver* s, double dt, bool project_b) {
+hipError_t current_step(tf_solver* s, const void* j, double dt, bool project_b) {
     const tf_grid& g = s->grid;
     const int ys = s->fast ? s->ystrip : 0;
+    const tf::RowMap rj(g.ny, g.nz / 2, s->rm.G);
     hipError_t e = timed(s, TF_PASS_OTHER, [&] {
-        return tf::launch_x_forward<T>(static_cast<const T*>(s->jstate), s->jspec, s->tw[0], g.nx, g.ny, g.nz, s->rm,
-                                       tf::Batch{}, s->stream);
+        return tf::launch_x_forward<T>(static_cast<const T*>(j), s->jspec, s->tw[0], g.nx, g.ny, g.nz / 2, rj, tf::Batch{},
+                                       s->stream);
     });
     if (e != hipSuccess) return e;
     e = timed(s, TF_PASS_OTHER, [&] {
-        return tf::launch_y_pass<T>(s->jspec, s->tw[1], g.nx, g.ny, g.nz, tf::Y_FORWARD, s->rm, ys, tf::Batch{}, s->stream);
+        return tf::launch_y_pass<T>(s->jspec, s->tw[1], g.nx, g.ny, g.nz / 2, tf::Y_FORWARD, rj, ys, tf::Batch{},
+                                    s->stream);
     });
     if (e != hipSuccess) return e;
     e = forward_xy<T>(s, TF_PASS_X_FORWARD, TF_PASS_Y_FORWARD);
     if (e != hipSuccess) return e;
     tf::StepParams p = step_params(s->grid, dt, project_b, s->zvariant);
     e = timed(s, TF_PASS_Z_STEP, [&] {
-        return tf::launch_z_current<T>(s->spec, s->jspec, s->tw[2], p, s->rm, s->stream);
+        return tf::launch_z_current<T>(s->spec, s->jspec, s->tw[2], p, s->rm, s->fast, s->stream);
     });
     if (e != hipSuccess) return e;
     e = timed(s, TF_PASS_Y_INVERSE, [&] {
@@ -683,34 +686,37 @@ tf_status tf_advance_current(tf_solver* s, const void* j, int32_t j_on_device, d
                                          " elements in LDS (float64: nz <= 768)");
     const size_t bytes6 = 6 * (size_t)s->cells * s->esize;
     const size_t spec_b = (size_t)s->grid.nz * s->grid.ny * s->nkx * 6 * 2 * s->esize;
-    if (!s->jstate || !s->jspec) {
+    // the current itself is copied only from the host, or from a device array
+    // that the x pass's 16-byte loads would find misaligned
+    const bool stage = !j_on_device || reinterpret_cast<uintptr_t>(j) % 16 != 0;
+    if (!s->jspec || (stage && !s->jstate)) {
         const size_t have = bytes6 + spec_b + 2 * s->esize * (size_t)(s->grid.nx + s->grid.ny + s->grid.nz);
         if (have + bytes6 + spec_b > device_cap())
             return fail(TF_ENOMEM, "current steps need " + std::to_string(bytes6 + spec_b) +
                                        " more device bytes, above TFOCUS_MAX_DEVICE_BYTES");
-        if (!s->jstate) {
-            hipError_t e = hipMalloc(&s->jstate, bytes6);
-            if (e != hipSuccess) {
-                s->jstate = nullptr;
-                return fail(e == hipErrorOutOfMemory ? TF_ENOMEM : TF_EDEVICE,
-                            std::string("current buffer: ") + hipGetErrorString(e));
-            }
-            TF_HIP(hipMemsetAsync(static_cast<char*>(s->jstate) + bytes6 / 2, 0, bytes6 / 2, s->stream));
+        auto alloc = [&](void** p, size_t bytes, const char* what) -> tf_status {
+            hipError_t e = hipMalloc(p, bytes);
+            if (e == hipSuccess) return TF_OK;
+            *p = nullptr;
+            return fail(e == hipErrorOutOfMemory ? TF_ENOMEM : TF_EDEVICE, std::string(what) + hipGetErrorString(e));
+        };
+        if (stage && !s->jstate) {
+            const tf_status st = alloc(&s->jstate, bytes6 / 2, "current buffer: ");
+            if (st != TF_OK) return st;
         }
         if (!s->jspec) {
-            hipError_t e = hipMalloc(&s->jspec, spec_b);
-            if (e != hipSuccess) {
-                s->jspec = nullptr;
-                return fail(e == hipErrorOutOfMemory ? TF_ENOMEM : TF_EDEVICE,
-                            std::string("current spectrum: ") + hipGetErrorString(e));
-            }
+            const tf_status st = alloc(&s->jspec, spec_b / 2, "current spectrum: ");
+            if (st != TF_OK) return st;
         }
     }
-    TF_HIP(hipMemcpyAsync(s->jstate, j, bytes6 / 2, j_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
-                          s->stream));
-    if (!j_on_device) TF_HIP(hipStreamSynchronize(s->stream));
+    if (stage) {
+        TF_HIP(hipMemcpyAsync(s->jstate, j, bytes6 / 2, j_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
+                              s->stream));
+        if (!j_on_device) TF_HIP(hipStreamSynchronize(s->stream));
+        j = s->jstate;
+    }
     const bool pb = s->project_b_next;
-    hipError_t e = s->prec == TF_F64 ? current_step<double>(s, dt, pb) : current_step<float>(s, dt, pb);
+    hipError_t e = s->prec == TF_F64 ? current_step<double>(s, j, dt, pb) : current_step<float>(s, j, dt, pb);
     if (e != hipSuccess) return fail(TF_EDEVICE, std::string("current step: ") + hipGetErrorString(e));
     s->project_b_next = false;
     s->t = s->t + dt;
