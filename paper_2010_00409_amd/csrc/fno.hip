@@ -100,19 +100,21 @@ __device__ __forceinline__ float ldf(const float* p) { return *p; }
 __device__ __forceinline__ float ldf(const bf16* p) { return (float)*p; }
 
 // ---------------------------------------------------------------------------
-// Generic strided GEMM  C[b] = alpha * A[b] (M x K) . B[b] (K x N)  (+= C[b])
+// Generic strided GEMM  C[b] = A[b] (M x K) . B[b] (K x N)
 // ---------------------------------------------------------------------------
 
 // Two-level affine index map: i -> (i >> sh) * hi + (i & (2^sh - 1)) * lo.
+// Within one batch entry every operand spans fewer than 2^31 elements (the
+// largest, the modes of 128 samples, 57 M).
 struct Ix {
     int sh, hi, lo;
 };
-__host__ __device__ __forceinline__ int64_t ixoff(Ix a, int i) {
-    return int64_t(i >> a.sh) * a.hi + int64_t(i & ((1 << a.sh) - 1)) * a.lo;
+__device__ __forceinline__ uint32_t ixoff(Ix a, int i) {
+    return uint32_t(i >> a.sh) * uint32_t(a.hi) + uint32_t(i & ((1 << a.sh) - 1)) * uint32_t(a.lo);
 }
 
 struct Operand {
-    const void* p;        // nullptr: every element is 1
+    const void* p;
     int64_t b1, b2;       // element strides of blockIdx.y and blockIdx.z
     Ix r, c;              // row and column maps
     int ones_from;        // rows >= ones_from read 1 (A only; large value: none)
@@ -123,8 +125,6 @@ struct Result {
     float* p;
     int64_t b1, b2;
     Ix r, c;
-    float alpha;
-    int accumulate;
 };
 struct GemmArgs {
     Operand a, b;
@@ -132,71 +132,95 @@ struct GemmArgs {
     int M, N, K;
 };
 
-__device__ __forceinline__ void ld4(const float* p, float v[4]) {
-    const float4 q = *(const float4*)p;
-    v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-}
-__device__ __forceinline__ void ld4(const bf16* p, float v[4]) {
-    const uint2 q = *(const uint2*)p;           // element 0 in the low half
-    v[0] = __uint_as_float(q.x << 16); v[1] = __uint_as_float(q.x & 0xffff0000u);
-    v[2] = __uint_as_float(q.y << 16); v[3] = __uint_as_float(q.y & 0xffff0000u);
-}
+template <typename T> struct Vec4;
+template <> struct Vec4<float> { typedef __attribute__((ext_vector_type(4))) float type; };
+template <> struct Vec4<bf16> { typedef __attribute__((ext_vector_type(4))) __bf16 type; };
 
-// Stage a ROWS x 32 slice of an operand in LDS as bf16 (hi and, for SPLIT,
-// lo parts), k contiguous.  "Rows" are the M index of A or the N index of B.
-// Each thread owns one row and 8 consecutive k and stores them with one
-// 16-byte LDS write per part.  Neighbouring threads take neighbouring k
-// groups when k is the contiguous index in memory (two 16-byte global loads
-// when aligned), else neighbouring rows (coalesced 4-byte loads); either way
-// the 16-byte writes of a quarter-wave start 20 banks apart (row pitch 80 B)
-// or are contiguous, so they do not collide.
-template <int ROWS, int NT, typename TT, bool SPLIT, bool IS_B>
-__device__ __forceinline__ void stage(bf16* s0, bf16* s1, const TT* P, const Operand& o, int r0, int k0, int nrows,
-                                      int K) {
-    constexpr int BK = 32, PITCH = BK + 8, KG = BK / 8;
-    auto off = [&](int gr, int gk) -> int64_t {
-        return IS_B ? ixoff(o.r, gk) + ixoff(o.c, gr) : ixoff(o.r, gr) + ixoff(o.c, gk);
-    };
-    for (int t = threadIdx.x; t < ROWS * KG; t += NT) {
-        int rr, kg;
+// One thread's share of a ROWS x 32 slice of an operand, on its way from memory
+// to LDS ("rows" are the M index of A or the N index of B).  Each item is one
+// row and 8 consecutive k, stored as bf16 (hi and, for SPLIT, lo parts), k
+// contiguous, with one 16-byte LDS write per part.  Neighbouring threads take
+// neighbouring k groups when k is the contiguous index in memory (two 4-element
+// loads when aligned), else neighbouring rows (coalesced single loads); either
+// way the 16-byte writes of a quarter-wave start 20 banks apart (row pitch 80 B)
+// or are contiguous, so they do not collide.  load() keeps the elements as they
+// are in memory, so that nothing waits for them before store(); positions past
+// the end are read from the last valid one and replaced in store().
+template <int ROWS, int NT, typename TT, bool SPLIT, bool IS_B> struct Slice {
+    static constexpr int BK = 32, PITCH = BK + 8, KG = BK / 8, ITEMS = ROWS * KG, IT = (ITEMS + NT - 1) / NT;
+    typedef typename Vec4<TT>::type V4;
+    V4 v[IT][2];
+
+    static __device__ __forceinline__ void item(const Operand& o, int it, int& rr, int& kg) {
+        const int t = (int(threadIdx.x) + it * NT) % ITEMS;
         if (o.fast_k) { rr = t / KG; kg = t % KG; }
         else          { rr = t % ROWS; kg = t / ROWS; }
-        const int gr = r0 + rr, gk0 = k0 + 8 * kg;
-        float v[8];
-        if (gr >= nrows) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = 0.0f;
-        } else if (!P || (!IS_B && gr >= o.ones_from)) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = gk0 + e < K ? 1.0f : 0.0f;
-        } else if (o.vec && o.fast_k && gk0 + 8 <= K) {
-            ld4(P + off(gr, gk0), v);
-            ld4(P + off(gr, gk0 + 4), v + 4);
-        } else if (gk0 + 8 <= K) {
-            const int64_t orow = IS_B ? ixoff(o.c, gr) : ixoff(o.r, gr);
-            const Ix kmap = IS_B ? o.r : o.c;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = ldf(P + orow + ixoff(kmap, gk0 + e));
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = gk0 + e < K ? ldf(P + off(gr, gk0 + e)) : 0.0f;
-        }
-        bf16x8 hi, lo;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const bf16 h = (bf16)v[e];
-            hi[e] = h;
-            lo[e] = (bf16)(v[e] - (float)h);
-        }
-        *(bf16x8*)&s0[rr * PITCH + 8 * kg] = hi;
-        if constexpr (SPLIT) *(bf16x8*)&s1[rr * PITCH + 8 * kg] = lo;
     }
-}
+    __device__ __forceinline__ void load(const TT* P, const Operand& o, const uint32_t* rowoff, int k0, int K) {
+        const Ix km = IS_B ? o.r : o.c;
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            int rr, kg;
+            item(o, it, rr, kg);
+            const int k = k0 + 8 * kg;
+            if (o.vec) {
+                v[it][0] = *(const V4*)(P + (rowoff[it] + ixoff(km, min(k, K - 4))));
+                v[it][1] = *(const V4*)(P + (rowoff[it] + ixoff(km, min(k + 4, K - 4))));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[it][e >> 2][e & 3] = P[rowoff[it] + ixoff(km, min(k + e, K - 1))];
+            }
+        }
+    }
+    static __device__ __forceinline__ void rows(uint32_t* rowoff, const Operand& o, int r0, int nrows) {
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            int rr, kg;
+            item(o, it, rr, kg);
+            const int last = (IS_B ? nrows : min(nrows, o.ones_from)) - 1;
+            rowoff[it] = ixoff(IS_B ? o.c : o.r, min(r0 + rr, last));
+        }
+    }
+    __device__ __forceinline__ void store(bf16* s0, bf16* s1, const Operand& o, int r0, int k0, int nrows,
+                                          int K) const {
+        const bool whole = r0 + ROWS <= (IS_B ? nrows : min(nrows, o.ones_from)) && k0 + BK <= K;
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            int rr, kg;
+            item(o, it, rr, kg);
+            if (ITEMS % NT != 0 && int(threadIdx.x) + it * NT >= ITEMS) break;
+            float f[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) f[e] = (float)v[it][e >> 2][e & 3];
+            if (!whole) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int gr = r0 + rr;
+                    if (!IS_B && gr >= o.ones_from) f[e] = 1.0f;
+                    if (gr >= nrows || k0 + 8 * kg + e >= K) f[e] = 0.0f;
+                }
+            }
+            bf16x8 hi, lo;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const bf16 h = (bf16)f[e];
+                hi[e] = h;
+                lo[e] = (bf16)(f[e] - (float)h);
+            }
+            *(bf16x8*)&s0[rr * PITCH + 8 * kg] = hi;
+            if constexpr (SPLIT) *(bf16x8*)&s1[rr * PITCH + 8 * kg] = lo;
+        }
+    }
+};
 
 // Each wave owns 32x32 output sub-tiles; the K loop stages 32-wide slices of
 // A and B in LDS as bf16 (hi and, for SPLIT, lo parts), k contiguous so each
-// lane reads its eight k values with one 16-byte LDS load.
-template <int BM, int BN, int NW, typename TA, typename TB, bool SPLIT>
+// lane reads its eight k values with one 16-byte LDS load.  DEPTH slices are in
+// flight in registers ahead of the one being multiplied: the two of a mode's
+// mixing (batch 1: 20 -> 15 us, the matrices' 57 MB bound it), one where the
+// slices of five blocks per CU cover the latency (the x contraction, 137 us at
+// 16 samples, 5.1 TB/s; with four in flight 160).
+template <int BM, int BN, int NW, typename TA, typename TB, bool SPLIT, int DEPTH>
 __global__ __launch_bounds__(64 * NW) void k_gemm(GemmArgs g) {
     constexpr int BK = 32, PITCH = BK + 8, NT = 64 * NW;
     constexpr int SUBN = BN / 32, SUB = (BM / 32) * SUBN, PER = SUB / NW;
@@ -209,8 +233,22 @@ __global__ __launch_bounds__(64 * NW) void k_gemm(GemmArgs g) {
     const int m0 = (blockIdx.x / tilesN) * BM, n0 = (blockIdx.x % tilesN) * BN;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int t = lane & 31, grp = lane >> 5;
-    const TA* A = g.a.p ? (const TA*)g.a.p + blockIdx.y * g.a.b1 + blockIdx.z * g.a.b2 : nullptr;
-    const TB* B = g.b.p ? (const TB*)g.b.p + blockIdx.y * g.b.b1 + blockIdx.z * g.b.b2 : nullptr;
+    const TA* A = (const TA*)g.a.p + blockIdx.y * g.a.b1 + blockIdx.z * g.a.b2;
+    const TB* B = (const TB*)g.b.p + blockIdx.y * g.b.b1 + blockIdx.z * g.b.b2;
+
+    typedef Slice<BM, NT, TA, SPLIT, false> SA;
+    typedef Slice<BN, NT, TB, SPLIT, true> SB;
+    SA ra[DEPTH];
+    SB rb[DEPTH];
+    uint32_t rowa[SA::IT], rowb[SB::IT];
+    SA::rows(rowa, g.a, m0, g.M);
+    SB::rows(rowb, g.b, n0, g.N);
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d)
+        if (d * BK < g.K) {
+            ra[d].load(A, g.a, rowa, d * BK, g.K);
+            rb[d].load(B, g.b, rowb, d * BK, g.K);
+        }
 
     f32x16 acc[PER];
 #pragma unroll
@@ -218,29 +256,38 @@ __global__ __launch_bounds__(64 * NW) void k_gemm(GemmArgs g) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[p][r] = 0.0f;
 
-    for (int k0 = 0; k0 < g.K; k0 += BK) {
-        stage<BM, NT, TA, SPLIT, false>(sa[0], sa[NP - 1], A, g.a, m0, k0, g.M, g.K);
-        stage<BN, NT, TB, SPLIT, true>(sb[0], sb[NP - 1], B, g.b, n0, k0, g.N, g.K);
-    __syncthreads();
+    for (int kb = 0; kb < g.K; kb += DEPTH * BK) {
 #pragma unroll
-        for (int p = 0; p < PER; ++p) {
-            const int st = wave * PER + p, mt = st / SUBN, nt = st % SUBN;
+        for (int d = 0; d < DEPTH; ++d) {
+            const int k0 = kb + d * BK;
+            if (k0 >= g.K) break;
+            ra[d].store(sa[0], sa[NP - 1], g.a, m0, k0, g.M, g.K);
+            rb[d].store(sb[0], sb[NP - 1], g.b, n0, k0, g.N, g.K);
+            if (k0 + DEPTH * BK < g.K) {
+                ra[d].load(A, g.a, rowa, k0 + DEPTH * BK, g.K);
+                rb[d].load(B, g.b, rowb, k0 + DEPTH * BK, g.K);
+            }
+            __syncthreads();
 #pragma unroll
-            for (int ks = 0; ks < BK / 16; ++ks) {
-                const int ao = (mt * 32 + t) * PITCH + ks * 16 + 8 * grp;
-                const int bo = (nt * 32 + t) * PITCH + ks * 16 + 8 * grp;
-                const bf16x8 ah = *(const bf16x8*)&sa[0][ao];
-                const bf16x8 bh = *(const bf16x8*)&sb[0][bo];
-                acc[p] = mfma(ah, bh, acc[p]);
-                if constexpr (SPLIT) {
-                    const bf16x8 al = *(const bf16x8*)&sa[NP - 1][ao];
-                    const bf16x8 bl = *(const bf16x8*)&sb[NP - 1][bo];
-                    acc[p] = mfma(ah, bl, acc[p]);
-                    acc[p] = mfma(al, bh, acc[p]);
+            for (int p = 0; p < PER; ++p) {
+                const int st = wave * PER + p, mt = st / SUBN, nt = st % SUBN;
+#pragma unroll
+                for (int ks = 0; ks < BK / 16; ++ks) {
+                    const int ao = (mt * 32 + t) * PITCH + ks * 16 + 8 * grp;
+                    const int bo = (nt * 32 + t) * PITCH + ks * 16 + 8 * grp;
+                    const bf16x8 ah = *(const bf16x8*)&sa[0][ao];
+                    const bf16x8 bh = *(const bf16x8*)&sb[0][bo];
+                    acc[p] = mfma(ah, bh, acc[p]);
+                    if constexpr (SPLIT) {
+                        const bf16x8 al = *(const bf16x8*)&sa[NP - 1][ao];
+                        const bf16x8 bl = *(const bf16x8*)&sb[NP - 1][bo];
+                        acc[p] = mfma(ah, bl, acc[p]);
+                        acc[p] = mfma(al, bh, acc[p]);
+                    }
                 }
             }
+            __syncthreads();
         }
-        __syncthreads();
     }
 
     float* Cp = g.c.p + blockIdx.y * g.c.b1 + blockIdx.z * g.c.b2;
@@ -248,15 +295,240 @@ __global__ __launch_bounds__(64 * NW) void k_gemm(GemmArgs g) {
     for (int p = 0; p < PER; ++p) {
         const int st = wave * PER + p, mt = st / SUBN, nt = st % SUBN;
         const int col = n0 + nt * 32 + t;
+        if (col >= g.N) continue;
+        float* Cc = Cp + ixoff(g.c.c, col);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int row = m0 + mt * 32 + 8 * (r >> 2) + 4 * grp + (r & 3);
-            if (row < g.M && col < g.N) {
-                float* d = Cp + ixoff(g.c.r, row) + ixoff(g.c.c, col);
-                const float v = g.c.alpha * acc[p][r];
-                *d = g.c.accumulate ? *d + v : v;
+            if (row < g.M) Cc[ixoff(g.c.r, row)] = acc[p][r];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// y and z transforms: out = A (M x K) . in, A one of the block DFT matrices
+// ---------------------------------------------------------------------------
+
+// in and out are the X1, X2 and mode layouts: rows (index, s) at (i >> 1) * hi +
+// (i & 1) * lo, LINE contiguous columns, one such matrix per (y, b).
+struct AxisArgs {
+    const float* A;       // [M][K]
+    const float* in;
+    float* out;
+    int in_hi, in_lo, out_hi, out_lo;
+    int64_t in_y, in_b, out_y, out_b;
+    int ny, nitems;       // an item: 32 columns of one matrix and MT row tiles
+};
+
+// element e of (hi, lo) <- bf16 split of v
+__device__ __forceinline__ void split(float v, bf16x8& hi, bf16x8& lo, int e) {
+    const bf16 h = (bf16)v;
+    hi[e] = h;
+    lo[e] = (bf16)(v - (float)h);
+}
+
+// A wave takes 32 columns and MT tiles of 32 rows of A at a time.  Its columns
+// are the B operand as they lie (lane (column, k group), 128 bytes per row and
+// group), so they go from memory to the MFMAs without LDS, and the registers of
+// a k step are refilled for the wave's next item as soon as they are split.  A
+// is split once per block into LDS in fragment order.  The order of the
+// products is that of k_gemm.  Memory bounds it; see launch_axis for MT.
+template <int M, int K, int MT>
+__global__ __launch_bounds__(256) void k_axis(AxisArgs a) {
+    constexpr int KN = K / 16, MTOT = (M + 31) / 32, MG = MTOT / MT, CG = LINE / 32;
+    __shared__ bf16x8 frag[KN * MTOT][2][64];
+    const int lane = threadIdx.x & 63, t = lane & 31, grp = lane >> 5;
+    const int stride = gridDim.x * 4;
+    int item = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    float v[KN][8];
+    auto column = [&](int i, int64_t y, int64_t b) {
+        const int q = i / MG / CG;
+        return int64_t(q / a.ny) * b + int64_t(q % a.ny) * y + (i / MG % CG) * 32;
+    };
+    auto load = [&](const float* src, int ks) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            v[ks][e] = (src + (8 * ks + (e >> 1)) * a.in_hi + (e & 1) * a.in_lo)[uint32_t(4 * grp * a.in_hi + t)];
+    };
+    {
+        const float* src = a.in + column(min(item, a.nitems - 1), a.in_y, a.in_b);
+#pragma unroll
+        for (int ks = 0; ks < KN; ++ks) load(src, ks);
+    }
+    for (int f = threadIdx.x; f < KN * MTOT * 64; f += 256) {
+        const int ft = f & 31, fg = (f >> 5) & 1, q = f >> 6, row = 32 * (q % MTOT) + ft;
+        const float* src = a.A + min(row, M - 1) * K + 16 * (q / MTOT) + 8 * fg;
+        const float4 u0 = *(const float4*)src, u1 = *(const float4*)(src + 4);
+        const float w[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
+        bf16x8 h, l;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) split(row < M ? w[e] : 0.0f, h, l, e);
+        frag[q][0][f & 63] = h;
+        frag[q][1][f & 63] = l;
+    }
+    __syncthreads();
+    while (item < a.nitems) {
+        const int next = item + stride, m0 = (item % MG) * MT;
+        int fl = lane;
+        asm volatile("" : "+v"(fl));     // A stays in LDS: hoisted out of the loop it takes half the registers
+        const float* src = a.in + column(min(next, a.nitems - 1), a.in_y, a.in_b);
+        f32x16 acc[MT];
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[m][r] = 0.0f;
+#pragma unroll
+        for (int ks = 0; ks < KN; ++ks) {
+            bf16x8 bh, bl;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) split(v[ks][e], bh, bl, e);
+            if (next < a.nitems) load(src, ks);
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                const bf16x8 ah = frag[ks * MTOT + m0 + m][0][fl], al = frag[ks * MTOT + m0 + m][1][fl];
+                acc[m] = mfma(ah, bh, acc[m]);
+                acc[m] = mfma(ah, bl, acc[m]);
+                acc[m] = mfma(al, bh, acc[m]);
             }
         }
+        float* dst = a.out + column(item, a.out_y, a.out_b);
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int r0 = 32 * (m0 + m) + 8 * (r >> 2) + (r & 3);   // + 4 grp: whole groups of 16 rows are valid
+                if (M % 32 == 0 || r0 < M)
+                    (dst + (r0 >> 1) * a.out_hi + (r0 & 1) * a.out_lo)[uint32_t(2 * grp * a.out_hi + t)] = acc[m][r];
+            }
+        item = next;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Weight gradients: part[b][chunk] = [A | 1]^T-style sums over CHUNK nodes
+// ---------------------------------------------------------------------------
+
+// Operand fragments of a 16-node step (lane: row or column t, nodes 8 grp + e),
+// read from memory as they lie.
+struct NodeFrag {                     // float [node][32]: one tile, bf16 hi + lo
+    static constexpr int TILES = 1;
+    static constexpr bool LO = true;
+    float v[8];
+    __device__ __forceinline__ void load(const void* p, int, int k, int t, int grp) {
+        const float* q = (const float*)p + int64_t(k) * C;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = (q + e * C)[uint32_t(8 * grp * C + t)];
+    }
+    __device__ __forceinline__ void get(int, bf16x8& hi, bf16x8& lo) const {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) split(v[e], hi, lo, e);
+    }
+};
+struct HiddenFrag {                   // bf16 [128][N3]: two tiles, exact
+    static constexpr int TILES = 2;
+    static constexpr bool LO = false;
+    bf16x8 v[2];
+    __device__ __forceinline__ void load(const void* p, int row0, int k, int t, int grp) {
+        const bf16* q = (const bf16*)p + int64_t(row0) * N3 + k;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) v[i] = *(const bf16x8*)&(q + 32 * i * N3)[uint32_t(t * N3 + 8 * grp)];
+    }
+    __device__ __forceinline__ void get(int i, bf16x8& hi, bf16x8& lo) const { hi = v[i]; lo = v[i]; }
+};
+struct OutFrag {                      // float [6][N3]: one tile of 6 columns, bf16 hi + lo
+    static constexpr int TILES = 1;
+    static constexpr bool LO = true;
+    float4 v[2];
+    __device__ __forceinline__ void load(const void* p, int, int k, int t, int grp) {
+        const float* q = (const float*)p + k;
+        const uint32_t off = uint32_t(min(t, NOUT - 1) * N3 + 8 * grp);
+        v[0] = *(const float4*)&q[off];
+        v[1] = *(const float4*)&(q + 4)[off];
+    }
+    __device__ __forceinline__ void get(int, bf16x8& hi, bf16x8& lo) const {
+        const float w[8] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) split(w[e], hi, lo, e);
+    }
+};
+
+struct GradArgs {
+    const void *a, *b;
+    int64_t a_b, b_b;     // bytes per sample
+    float* part;          // [B][NCHUNK][rows + 1][cols], the last row the sums of b
+    int rows, cols;
+};
+
+// One wave per sample, chunk and pair of hidden-unit tiles walks its 4096 nodes
+// in steps of 16, the order of the products that of k_gemm; the row of ones
+// that gives the bias gradient is a constant A operand.  A wave's loads bound
+// it, there being one or two waves per SIMD at 16 samples: DEPTH steps are in
+// flight in registers.  16 samples: [W; b] 442 us through LDS -> LIN, [P1; c1]
+// 514 -> LP1, [P2; c2] 652 -> LP2.
+template <typename FA, typename FB>
+__global__ __launch_bounds__(64) void k_wgrad(GradArgs a) {
+    constexpr int DEPTH = 8, TA = FA::TILES, TB = FB::TILES;
+    const int t = threadIdx.x & 31, grp = threadIdx.x >> 5;
+    const int tile0 = 2 * blockIdx.x, k0 = blockIdx.y * CHUNK;
+    const char* A = (const char*)a.a + blockIdx.z * a.a_b;
+    const char* B = (const char*)a.b + blockIdx.z * a.b_b;
+    FA fa[DEPTH];
+    FB fb[DEPTH];
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+        fa[d].load(A, 32 * tile0, k0 + 16 * d, t, grp);
+        fb[d].load(B, 32 * tile0, k0 + 16 * d, t, grp);
+    }
+    f32x16 acc[TA][TB], ones[TB];
+    bf16x8 one;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) one[e] = (bf16)1.0f;
+#pragma unroll
+    for (int j = 0; j < TB; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            ones[j][r] = 0.0f;
+#pragma unroll
+            for (int i = 0; i < TA; ++i) acc[i][j][r] = 0.0f;
+        }
+    for (int k = 0; k < CHUNK; k += 16 * DEPTH) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            bf16x8 ah[TA], al[TA], bh[TB], bl[TB];
+#pragma unroll
+            for (int i = 0; i < TA; ++i) fa[d].get(i, ah[i], al[i]);
+#pragma unroll
+            for (int j = 0; j < TB; ++j) fb[d].get(j, bh[j], bl[j]);
+            const int kn = k + 16 * (d + DEPTH);
+            if (kn < CHUNK) {
+                fa[d].load(A, 32 * tile0, k0 + kn, t, grp);
+                fb[d].load(B, 32 * tile0, k0 + kn, t, grp);
+            }
+#pragma unroll
+            for (int j = 0; j < TB; ++j) {
+#pragma unroll
+                for (int i = 0; i < TA; ++i) {
+                    acc[i][j] = mfma(ah[i], bh[j], acc[i][j]);
+                    if constexpr (FB::LO) acc[i][j] = mfma(ah[i], bl[j], acc[i][j]);
+                    if constexpr (FA::LO) acc[i][j] = mfma(al[i], bh[j], acc[i][j]);
+                }
+                ones[j] = mfma(one, bh[j], ones[j]);
+                if constexpr (FB::LO) ones[j] = mfma(one, bl[j], ones[j]);
+            }
+        }
+    }
+    float* o = a.part + (int64_t(blockIdx.z) * NCHUNK + blockIdx.y) * (a.rows + 1) * a.cols;
+    const int row0 = TA == 2 ? 32 * tile0 : 0, col0 = TB == 2 ? 32 * tile0 : 0;
+#pragma unroll
+    for (int j = 0; j < TB; ++j) {
+        const int col = col0 + 32 * j + t;
+        if (col >= a.cols) continue;
+#pragma unroll
+        for (int i = 0; i < TA; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                o[(row0 + 32 * i + 8 * (r >> 2) + 4 * grp + (r & 3)) * a.cols + col] = acc[i][j][r];
+        if (grp == 0 && row0 == 0) o[a.rows * a.cols + col] = ones[j][0];
     }
 }
 
@@ -561,13 +833,6 @@ __device__ __forceinline__ void ld4c(const float* p, bool in, float v[4]) {
     } else {
         v[0] = v[1] = v[2] = v[3] = 0.0f;
     }
-}
-
-// element e of (hi, lo) <- bf16 split of v
-__device__ __forceinline__ void split(float v, bf16x8& hi, bf16x8& lo, int e) {
-    const bf16 h = (bf16)v;
-    hi[e] = h;
-    lo[e] = (bf16)(v - (float)h);
 }
 
 struct InfArgs {
@@ -964,15 +1229,34 @@ __global__ void k_fold_r(const float* gs, float* gr) {
 
 // bf16 working copy of R as the real block matrix R*[(s,c)][(s',o)]:
 //   s = s': re,  s = 0, s' = 1: im,  s = 1, s' = 0: -im
-__global__ void k_expand_r(const float* r, bf16* rb) {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= int64_t(NMODES) * 4096) return;
-    const int j = i & 63, k = (i >> 6) & 63;
-    const int64_t q = i >> 12;
-    const int s = k >> 5, c = k & 31, s2 = j >> 5, o = j & 31;
-    const float* e = r + ((q * C + c) * C + o) * 2;
-    const float v = s == s2 ? e[0] : (s == 0 ? e[1] : -e[1]);
-    rb[i] = (bf16)v;
+// as it is for a surrogate that trains, whose adjoint mixing contracts over
+// (s',o), and transposed, R*^T[(s',o)][(s,c)], for one that only infers (the
+// forward mixing contracts over (s,c), and reads it 16 bytes at a time).
+// One block per mode: R is read once into LDS, and every thread writes 16
+// bytes of two rows of the block (one element per thread took 67 us, 1.3 TB/s).
+__global__ __launch_bounds__(256) void k_expand_r(const float* r, bf16* rb, int transposed) {
+    const int64_t q = blockIdx.x;
+    __shared__ float2 e[C * (C + 1)];
+    const float4* src = (const float4*)(r + q * C * C * 2);
+    for (int i = threadIdx.x; i < C * C / 2; i += 256) {
+        const float4 v = src[i];
+        const int c = (2 * i) / C, o = (2 * i) % C;
+        e[c * (C + 1) + o] = make_float2(v.x, v.y);
+        e[c * (C + 1) + o + 1] = make_float2(v.z, v.w);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int i = threadIdx.x + 256 * h, row = i >> 3, col0 = 8 * (i & 7);
+        bf16x8 v;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            const int k = transposed ? col0 + x : row, j = transposed ? row : col0 + x;
+            const float2 f = e[(k & 31) * (C + 1) + (j & 31)];
+            v[x] = (bf16)((k >> 5) == (j >> 5) ? f.x : (k >> 5) == 0 ? f.y : -f.y);
+        }
+        *(bf16x8*)&rb[q * 4096 + 8 * i] = v;
+    }
 }
 
 // Effective projection of sample b for a head of nb basis fields:
@@ -1103,10 +1387,10 @@ inline int64_t max_ix(Ix a, int n) {
 
 typedef void (*GemmLaunch)(const GemmArgs&, int, int, hipStream_t);
 
-template <int BM, int BN, int NW, typename TA, typename TB, bool SPLIT>
+template <int BM, int BN, int NW, typename TA, typename TB, bool SPLIT, int DEPTH>
 void launch(const GemmArgs& g, int by, int bz, hipStream_t st) {
     const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
-    hipLaunchKernelGGL((k_gemm<BM, BN, NW, TA, TB, SPLIT>), dim3(tiles, by, bz), dim3(64 * NW), 0, st, g);
+    hipLaunchKernelGGL((k_gemm<BM, BN, NW, TA, TB, SPLIT, DEPTH>), dim3(tiles, by, bz), dim3(64 * NW), 0, st, g);
 }
 
 struct Gemm {
@@ -1117,9 +1401,7 @@ struct Gemm {
 
 // Checks an operand against the size of the buffer it addresses.
 inline bool fits(const Operand& o, int rows, int cols, int by, int bz, int64_t size) {
-    if (!o.p) return true;
     const int r = std::min(rows, o.ones_from);
-    if (r <= 0) return true;
     const int64_t mx = int64_t(by - 1) * o.b1 + int64_t(bz - 1) * o.b2 + max_ix(o.r, r) + max_ix(o.c, cols);
     return mx < size;
 }
@@ -1137,7 +1419,7 @@ inline Operand opnd(const void* p, Ix r, Ix c, int64_t b1, int64_t b2, int fast_
 // from ones_from on are never loaded (stage takes them first), so they do
 // not bar the vector loads of the others.
 inline bool vec_ok(const Operand& o, int rows, int cols, bool is_b, size_t elem) {
-    if (!o.p || !o.fast_k) return false;
+    if (!o.fast_k) return false;
     const bool k_is_row = is_b;                 // A: (M, K); B: (K, N)
     const Ix fast = o.fast_k ? (k_is_row ? o.r : o.c) : (k_is_row ? o.c : o.r);
     const Ix slow = o.fast_k ? (k_is_row ? o.c : o.r) : (k_is_row ? o.r : o.c);
@@ -1149,8 +1431,8 @@ inline bool vec_ok(const Operand& o, int rows, int cols, bool is_b, size_t elem)
     if (!mult4(o.b1) || !mult4(o.b2)) return false;
     return (uintptr_t)o.p % (4 * elem) == 0;
 }
-inline Result res(float* p, Ix r, Ix c, int64_t b1, int64_t b2, float alpha = 1.0f, int acc = 0) {
-    return Result{p, b1, b2, r, c, alpha, acc};
+inline Result res(float* p, Ix r, Ix c, int64_t b1, int64_t b2) {
+    return Result{p, b1, b2, r, c};
 }
 
 // DFT tables, float64-built from the exact integer phase (j k mod P), for
@@ -1301,57 +1583,71 @@ Gemm g_xcontract(const float* A, const float* in, float* out, int B) {
     GemmArgs g{opnd(A, plain(N), plain(1), 0, 0, 1),
                opnd(in, plain(C), two(5, N * C, 1), 0, NODE_SZ, 0),
                res(out, plain(C), two(5, 2 * LINE, 1), 0, X1_SZ), 24, N * N * C, N};
-    return Gemm{g, 1, B, launch<32, 128, 4, float, float, true>};
+    return Gemm{g, 1, B, launch<32, 128, 4, float, float, true, 1>};
+}
+// The y and z transforms of B samples.  MT = all row tiles of A per wave reads
+// the input once (batch 64, the twelve of a pass: 2.14 ms through k_gemm, 1.79
+// so, 5.1 TB/s); below FEW waves (one per SIMD) the tiles go to waves of their
+// own, which share the columns through the L1 (batch 1: 11 -> 6.7 us each).
+template <int M, int K>
+tf_status axis(tf_fno* f, const float* A, const float* in, float* out, int ny, Ix in_k, Ix out_r, int64_t in_y,
+               int64_t in_b, int64_t out_y, int64_t out_b, int B) {
+    constexpr int MTOT = (M + 31) / 32, FEW = 1024;
+    const auto hi = [](Ix x) { return x.sh == 1 ? x.hi : 2 * x.lo; };
+    AxisArgs a{A, in, out, hi(in_k), in_k.lo, hi(out_r), out_r.lo, in_y, in_b, out_y, out_b, ny, 0};
+    const int cols = B * ny * (LINE / 32);
+    const auto go = [&](auto kernel, int items) {
+        a.nitems = items;
+        // at most four blocks per CU: a wave takes several items, and A is split less often
+        hipLaunchKernelGGL(kernel, dim3(std::min((items + 3) / 4, 1024)), dim3(256), 0, f->cur, a);
+    };
+    if (cols < FEW) go(k_axis<M, K, 1>, cols * MTOT);
+    else go(k_axis<M, K, MTOT>, cols);
+    return launched();
 }
 // y contraction (per z): X1 layout in, X2 layout out; A is 48 x 128
-Gemm g_ycontract(const float* A, const float* in, float* out, int B) {
-    GemmArgs g{opnd(A, plain(128), plain(1), 0, 0, 1),
-               opnd(in, plain(LINE), plain(1), int64_t(N) * 2 * LINE, X1_SZ, 0),
-               res(out, two(1, N * 2 * LINE, LINE), plain(1), 2 * LINE, X2_SZ), 48, LINE, 128};
-    return Gemm{g, N, B, launch<64, 128, 4, float, float, true>};
+tf_status ycontract(tf_fno* f, const float* A, const float* in, float* out, int B) {
+    return axis<48, 128>(f, A, in, out, N, plain(LINE), two(1, N * 2 * LINE, LINE), int64_t(N) * 2 * LINE, X1_SZ,
+                         2 * LINE, X2_SZ, B);
 }
 // z contraction (per ky): X2 layout in, mode layout out
-Gemm g_zcontract(const float* A, const float* in, float* out, int B) {
-    GemmArgs g{opnd(A, plain(128), plain(1), 0, 0, 1),
-               opnd(in, plain(LINE), plain(1), int64_t(N) * 2 * LINE, X2_SZ, 0),
-               res(out, plain(KS * LINE), plain(1), LINE, X3_SZ), 48, LINE, 128};
-    return Gemm{g, KS, B, launch<64, 128, 4, float, float, true>};
+tf_status zcontract(tf_fno* f, const float* A, const float* in, float* out, int B) {
+    return axis<48, 128>(f, A, in, out, KS, plain(LINE), plain(KS * LINE), int64_t(N) * 2 * LINE, X2_SZ, LINE, X3_SZ,
+                         B);
 }
 // z expansion (per ky): mode layout in, X2 layout out; A is 128 x 48
-Gemm g_zexpand(const float* A, const float* in, float* out, int B) {
-    GemmArgs g{opnd(A, plain(48), plain(1), 0, 0, 1),
-               opnd(in, plain(KS * LINE), plain(1), LINE, X3_SZ, 0),
-               res(out, plain(LINE), plain(1), int64_t(N) * 2 * LINE, X2_SZ), 128, LINE, 48};
-    return Gemm{g, KS, B, launch<64, 128, 4, float, float, true>};
+tf_status zexpand(tf_fno* f, const float* A, const float* in, float* out, int B) {
+    return axis<128, 48>(f, A, in, out, KS, plain(KS * LINE), plain(LINE), LINE, X3_SZ, int64_t(N) * 2 * LINE, X2_SZ,
+                         B);
 }
 // y expansion (per z): X2 layout in, X1 layout out
-Gemm g_yexpand(const float* A, const float* in, float* out, int B) {
-    GemmArgs g{opnd(A, plain(48), plain(1), 0, 0, 1),
-               opnd(in, two(1, N * 2 * LINE, LINE), plain(1), 2 * LINE, X2_SZ, 0),
-               res(out, plain(LINE), plain(1), int64_t(N) * 2 * LINE, X1_SZ), 128, LINE, 48};
-    return Gemm{g, N, B, launch<64, 128, 4, float, float, true>};
+tf_status yexpand(tf_fno* f, const float* A, const float* in, float* out, int B) {
+    return axis<128, 48>(f, A, in, out, N, two(1, N * 2 * LINE, LINE), plain(LINE), 2 * LINE, X2_SZ,
+                         int64_t(N) * 2 * LINE, X1_SZ, B);
 }
 
 // ---- per-mode complex channel mixing as real 64 x 64 blocks ----
 // mode q = kz * 288 + (ky * 12 + kx): blockIdx.y = ky * 12 + kx, blockIdx.z = kz
 constexpr int64_t MODE_Y = C, MODE_Z = 2 * KS * LINE;
 
-// Y*[b][(s',o)] = sum X*[b][(s,c)] Wq[(s,c)][(s',o)]  (trans: Wq^T)
-Gemm g_mix(const float* X, const bf16* R, float* Yo, int B, bool trans) {
-    const Ix rr = trans ? plain(1) : plain(64), rc = trans ? plain(64) : plain(1);
+// Y*[b][(s',o)] = sum X*[b][(s,c)] Wq[(s,c)][(s',o)]  (trans: Wq^T); kfast:
+// R holds the matrices with the contracted index contiguous
+Gemm g_mix(const float* X, const bf16* R, float* Yo, int B, bool trans, bool kfast) {
+    const Ix rr = kfast ? plain(1) : plain(64), rc = kfast ? plain(64) : plain(1);
     GemmArgs g{opnd(X, plain(X3_SZ), two(5, KS * LINE, 1), MODE_Y, MODE_Z, 1),
-               opnd(R, rr, rc, 4096, int64_t(KS * M) * 4096, trans ? 1 : 0),
+               opnd(R, rr, rc, 4096, int64_t(KS * M) * 4096, kfast ? 1 : 0),
                res(Yo, plain(X3_SZ), two(5, KS * LINE, 1), MODE_Y, MODE_Z), B, 64, 64};
     // the adjoint (trans) splits the gradient operand into bf16 hi + lo; the
     // forward keeps one bf16 copy of the modes
-    return Gemm{g, KS * M, KS, trans ? launch<32, 64, 2, float, bf16, true> : launch<32, 64, 2, float, bf16, false>};
+    return Gemm{g, KS * M, KS, trans ? launch<32, 64, 2, float, bf16, true, 2>
+                                        : launch<32, 64, 2, float, bf16, false, 2>};
 }
 // G*[q][(s,c)][(s',o)] = sum_b X*[b][(s,c)] gY*[b][(s',o)]
 Gemm g_mix_grad(const float* X, const float* gY, float* gs, int B) {
     GemmArgs g{opnd(X, two(5, KS * LINE, 1), plain(X3_SZ), MODE_Y, MODE_Z, 0),
                opnd(gY, plain(X3_SZ), two(5, KS * LINE, 1), MODE_Y, MODE_Z, 0),
                res(gs, plain(64), plain(1), 4096, int64_t(KS * M) * 4096), 64, 64, B};
-    return Gemm{g, KS * M, KS, launch<64, 64, 4, float, float, true>};
+    return Gemm{g, KS * M, KS, launch<64, 64, 4, float, float, true, 1>};
 }
 
 }  // namespace
@@ -1514,8 +1810,8 @@ tf_status refresh_working(tf_fno* f) {
     for (int l = 0; l < LAYERS; ++l) {
         hipLaunchKernelGGL(k_to_bf16, dim3((C * C + 255) / 256), dim3(256), 0, f->cur, f->prm + off_w(l), f->wb[l],
                            C * C);
-        const int64_t n = int64_t(NMODES) * 4096;
-        hipLaunchKernelGGL(k_expand_r, dim3((n + 255) / 256), dim3(256), 0, f->cur, f->prm + off_r(l), f->rb[l]);
+        hipLaunchKernelGGL(k_expand_r, dim3(NMODES), dim3(256), 0, f->cur, f->prm + off_r(l), f->rb[l],
+                           f->training ? 0 : 1);
     }
     hipLaunchKernelGGL(k_to_bf16, dim3((C * HID + 255) / 256), dim3(256), 0, f->cur, f->prm + OFF_P1, f->p1b, C * HID);
     hipLaunchKernelGGL(k_p1_kappa, dim3((C * HID + 255) / 256), dim3(256), 0, f->cur, f->prm + OFF_P1, f->p1k);
@@ -1542,16 +1838,16 @@ tf_status forward_body(tf_fno* f, const float* params, const float* hw, int B, f
                            f->prm + OFF_B0, f->V[0], tot);
         TRY(launched());
     }
-    const int64_t szN = nb * NODE_SZ, sz1 = nb * X1_SZ, sz2 = nb * X2_SZ, sz3 = nb * X3_SZ;
+    const int64_t szN = nb * NODE_SZ, sz1 = nb * X1_SZ, sz3 = nb * X3_SZ;
     float* v = f->V[0];
     for (int l = 0; l < LAYERS; ++l) {
         float* modes = f->training ? f->X3[l] : f->X3[0];
         TRY(run(f, g_xcontract(f->fx, v, f->T1, B), 24 * N, szN, sz1));
-        TRY(run(f, g_ycontract(f->fs, f->T1, f->T2, B), 48 * 128, sz1, sz2));
-        TRY(run(f, g_zcontract(f->fs, f->T2, modes, B), 48 * 128, sz2, sz3));
-        TRY(run(f, g_mix(modes, f->rb[l], f->Y, B, false), sz3, int64_t(NMODES) * 4096, sz3, 4, 2));
-        TRY(run(f, g_zexpand(f->gs, f->Y, f->T2, B), 128 * 48, sz3, sz2));
-        TRY(run(f, g_yexpand(f->gs, f->T2, f->T1, B), 128 * 48, sz2, sz1));
+        TRY(ycontract(f, f->fs, f->T1, f->T2, B));
+        TRY(zcontract(f, f->fs, f->T2, modes, B));
+        TRY(run(f, g_mix(modes, f->rb[l], f->Y, B, false, false), sz3, int64_t(NMODES) * 4096, sz3, 4, 2));
+        TRY(zexpand(f, f->gs, f->Y, f->T2, B));
+        TRY(yexpand(f, f->gs, f->T2, f->T1, B));
         float* nv = f->training ? f->V[l + 1] : (v == f->V[0] ? f->V[1] : f->V[0]);
         LineArgs a{f->gx, f->T1, v, f->wb[l], f->prm + off_b(l), nullptr,
                    (f->training && l < LAYERS - 1) ? f->Z[l] : nullptr, nv, B * N * N, 0, l < LAYERS - 1};
@@ -1569,7 +1865,7 @@ tf_status forward_body(tf_fno* f, const float* params, const float* hw, int B, f
 // contractions, mixing and expansions, and one fused x-line kernel.
 tf_status forward_infer(tf_fno* f, const float* params, int B, float* out) {
     const int64_t nb = B;
-    const int64_t sz1 = nb * X1_SZ, sz2 = nb * X2_SZ, sz3 = nb * X3_SZ;
+    const int64_t sz3 = nb * X3_SZ;
     const int lines = B * N * N;
     InfArgs a{f->gx, f->fx, f->T1, nullptr, params, f->prm + OFF_W0, f->prm + OFF_B0, nullptr, nullptr,
               nullptr, f->T1, f->p1k, f->prm + OFF_C1, f->p2k, f->c2e, out, lines};
@@ -1577,11 +1873,11 @@ tf_status forward_infer(tf_fno* f, const float* params, int B, float* out) {
     TRY(launched());
     const float* v = nullptr;                 // v_0 is recomputed, never stored
     for (int l = 0; l < LAYERS; ++l) {
-        TRY(run(f, g_ycontract(f->fs, f->T1, f->T2, B), 48 * 128, sz1, sz2));
-        TRY(run(f, g_zcontract(f->fs, f->T2, f->X3[0], B), 48 * 128, sz2, sz3));
-        TRY(run(f, g_mix(f->X3[0], f->rb[l], f->Y, B, false), sz3, int64_t(NMODES) * 4096, sz3, 4, 2));
-        TRY(run(f, g_zexpand(f->gs, f->Y, f->T2, B), 128 * 48, sz3, sz2));
-        TRY(run(f, g_yexpand(f->gs, f->T2, f->T1, B), 128 * 48, sz2, sz1));
+        TRY(ycontract(f, f->fs, f->T1, f->T2, B));
+        TRY(zcontract(f, f->fs, f->T2, f->X3[0], B));
+        TRY(run(f, g_mix(f->X3[0], f->rb[l], f->Y, B, false, true), sz3, int64_t(NMODES) * 4096, sz3, 4, 2));
+        TRY(zexpand(f, f->gs, f->Y, f->T2, B));
+        TRY(yexpand(f, f->gs, f->T2, f->T1, B));
         a.act = v;
         a.w = f->wb[l];
         a.bias = f->prm + off_b(l);
@@ -1616,8 +1912,8 @@ tf_status reduce_into(tf_fno* f, int nparts, int len, float* dst, int groups = 1
 // The bf16 weights themselves are exact in either form.
 tf_status backward(tf_fno* f, const float* params, const float* hw, const float* target, int B) {
     const int64_t nb = B;
-    const int64_t szN = nb * NODE_SZ, sz1 = nb * X1_SZ, sz2 = nb * X2_SZ, sz3 = nb * X3_SZ;
-    const int64_t szO = nb * OUT_SZ, szH = nb * HID * N3, szP = nb * NCHUNK * 33 * HID;
+    const int64_t szN = nb * NODE_SZ, sz1 = nb * X1_SZ, sz3 = nb * X3_SZ;
+    const int64_t szO = nb * OUT_SZ;
     // loss and dL/dout
     hipLaunchKernelGGL(k_loss_part, dim3(LOSS_CH, B), dim3(256), 0, f->cur, f->out, target, f->lpart);
     hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(LOSS_THREADS), 0, f->cur, f->lpart, LOSS_CH, B, f->dres,
@@ -1631,17 +1927,15 @@ tf_status backward(tf_fno* f, const float* params, const float* hw, const float*
     hipLaunchKernelGGL(k_proj, dim3((p.ntiles + 3) / 4), dim3(256), 0, f->cur, p);
     TRY(launched());
     {   // [P1; c1] = [v3 | 1]^T dL/dpre
-        GemmArgs a{opnd(f->V[3], plain(1), plain(C), int64_t(CHUNK) * C, NODE_SZ, 0, C),
-                   opnd(f->ghT, plain(1), plain(N3), CHUNK, int64_t(HID) * N3, 1),
-                   res(f->part, plain(HID), plain(1), 33 * HID, int64_t(NCHUNK) * 33 * HID), 33, HID, CHUNK};
-        TRY(run(f, Gemm{a, NCHUNK, B, launch<64, 128, 4, float, bf16, true>}, szN, szH, szP, 4, 2));
+        GradArgs a{f->V[3], f->ghT, NODE_SZ * 4, int64_t(HID) * N3 * 2, f->part, C, HID};
+        hipLaunchKernelGGL((k_wgrad<NodeFrag, HiddenFrag>), dim3(HID / 64, NCHUNK, B), dim3(64), 0, f->cur, a);
+        TRY(launched());
         TRY(reduce_into(f, B * NCHUNK, 33 * HID, f->grad + OFF_P1));
     }
     {   // [P2; c2] = [h | 1]^T dL/dout
-        GemmArgs a{opnd(f->hT, plain(N3), plain(1), CHUNK, int64_t(HID) * N3, 1, HID),
-                   opnd(f->gout, plain(1), plain(N3), CHUNK, OUT_SZ, 1),
-                   res(f->part, plain(NOUT), plain(1), 129 * NOUT, int64_t(NCHUNK) * 129 * NOUT), 129, NOUT, CHUNK};
-        TRY(run(f, Gemm{a, NCHUNK, B, launch<32, 32, 1, bf16, float, true>}, szH, szO, szP, 2, 4));
+        GradArgs a{f->hT, f->gout, int64_t(HID) * N3 * 2, OUT_SZ * 4, f->part, HID, NOUT};
+        hipLaunchKernelGGL((k_wgrad<HiddenFrag, OutFrag>), dim3(HID / 64, NCHUNK, B), dim3(64), 0, f->cur, a);
+        TRY(launched());
         // per-sample gradient of the effective head, then through the head weights
         TRY(reduce_into(f, NCHUNK, 129 * NOUT, f->geff, B));
         const int n = (HID + 1) * NOUT * f->nb;
@@ -1652,16 +1946,15 @@ tf_status backward(tf_fno* f, const float* params, const float* hw, const float*
     for (int l = LAYERS - 1; l >= 0; --l) {
         float* gn = g == f->G[0] ? f->G[1] : f->G[0];
         {   // [W_l; b_l] = [v_l | 1]^T dL/dz_l
-            GemmArgs a{opnd(f->V[l], plain(1), plain(C), int64_t(CHUNK) * C, NODE_SZ, 0, C),
-                       opnd(g, plain(C), plain(1), int64_t(CHUNK) * C, NODE_SZ, 0),
-                       res(f->part, plain(C), plain(1), 33 * C, int64_t(NCHUNK) * 33 * C), 33, C, CHUNK};
-            TRY(run(f, Gemm{a, NCHUNK, B, launch<64, 32, 2, float, float, true>}, szN, szN, szP));
+            GradArgs a{f->V[l], g, NODE_SZ * 4, NODE_SZ * 4, f->part, C, C};
+            hipLaunchKernelGGL((k_wgrad<NodeFrag, NodeFrag>), dim3(1, NCHUNK, B), dim3(64), 0, f->cur, a);
+            TRY(launched());
             TRY(reduce_into(f, B * NCHUNK, 33 * C, f->grad + off_w(l)));
         }
         // adjoint of the inverse transform: modes gradient
         TRY(run(f, g_xcontract(f->gxT, g, f->T1, B), 24 * N, szN, sz1));
-        TRY(run(f, g_ycontract(f->gsT, f->T1, f->T2, B), 48 * 128, sz1, sz2));
-        TRY(run(f, g_zcontract(f->gsT, f->T2, f->Y, B), 48 * 128, sz2, sz3));
+        TRY(ycontract(f, f->gsT, f->T1, f->T2, B));
+        TRY(zcontract(f, f->gsT, f->T2, f->Y, B));
         // mixing: dR and dX
         TRY(run(f, g_mix_grad(f->X3[l], f->Y, f->gstar, B), sz3, sz3, int64_t(NMODES) * 4096));
         {
@@ -1669,10 +1962,10 @@ tf_status backward(tf_fno* f, const float* params, const float* hw, const float*
             hipLaunchKernelGGL(k_fold_r, dim3((n + 255) / 256), dim3(256), 0, f->cur, f->gstar, f->grad + off_r(l));
             TRY(launched());
         }
-        TRY(run(f, g_mix(f->Y, f->rb[l], f->Y2, B, true), sz3, int64_t(NMODES) * 4096, sz3, 4, 2));
+        TRY(run(f, g_mix(f->Y, f->rb[l], f->Y2, B, true, true), sz3, int64_t(NMODES) * 4096, sz3, 4, 2));
         // adjoint of the forward transform, then the x line with the pointwise branch
-        TRY(run(f, g_zexpand(f->fsT, f->Y2, f->T2, B), 128 * 48, sz3, sz2));
-        TRY(run(f, g_yexpand(f->fsT, f->T2, f->T1, B), 128 * 48, sz2, sz1));
+        TRY(zexpand(f, f->fsT, f->Y2, f->T2, B));
+        TRY(yexpand(f, f->fsT, f->T2, f->T1, B));
         LineArgs a{f->fxT, f->T1, g, f->wb[l], nullptr, l > 0 ? f->Z[l - 1] : nullptr, nullptr, gn, B * N * N, 1, 0};
         hipLaunchKernelGGL(k_lineout, dim3((B * N * N + 3) / 4), dim3(256), 0, f->cur, a);
         TRY(launched());
@@ -1951,18 +2244,16 @@ tf_status tf_fno_eval(tf_fno* f, const float* params, const float* head_w, const
 tf_status tf_fno_spectral_forward(tf_fno* f, const float* v, int32_t batch, float* modes) {
     TRY(check_batch(f, batch, nullptr, false));
     if (!v || !modes) return fail(TF_EINVAL, "NULL argument");
-    const int64_t nb = batch;
-    TRY(run(f, g_xcontract(f->fx, v, f->T1, batch), 24 * N, nb * NODE_SZ, nb * X1_SZ));
-    TRY(run(f, g_ycontract(f->fs, f->T1, f->T2, batch), 48 * 128, nb * X1_SZ, nb * X2_SZ));
-    return run(f, g_zcontract(f->fs, f->T2, modes, batch), 48 * 128, nb * X2_SZ, nb * X3_SZ);
+    TRY(run(f, g_xcontract(f->fx, v, f->T1, batch), 24 * N, batch * NODE_SZ, batch * X1_SZ));
+    TRY(ycontract(f, f->fs, f->T1, f->T2, batch));
+    return zcontract(f, f->fs, f->T2, modes, batch);
 }
 
 tf_status tf_fno_spectral_inverse(tf_fno* f, const float* modes, int32_t batch, float* u) {
     TRY(check_batch(f, batch, nullptr, false));
     if (!modes || !u) return fail(TF_EINVAL, "NULL argument");
-    const int64_t nb = batch;
-    TRY(run(f, g_zexpand(f->gs, modes, f->T2, batch), 128 * 48, nb * X3_SZ, nb * X2_SZ));
-    TRY(run(f, g_yexpand(f->gs, f->T2, f->T1, batch), 128 * 48, nb * X2_SZ, nb * X1_SZ));
+    TRY(zexpand(f, f->gs, modes, f->T2, batch));
+    TRY(yexpand(f, f->gs, f->T2, f->T1, batch));
     LineArgs a{f->gx, f->T1, nullptr, f->wb[0], nullptr, nullptr, nullptr, u, batch * N * N, 0, 0};
     hipLaunchKernelGGL(k_lineout, dim3((batch * N * N + 3) / 4), dim3(256), 0, f->cur, a);
     return launched();
