@@ -85,7 +85,7 @@ __device__ __forceinline__ float erf_as(float u) {
                                 a * (0.0001520143f + a * (0.0002765672f + a * 0.0000430638f)))));
     const float q2 = q * q, q4 = q2 * q2, q8 = q4 * q4;
     const float r = 1.0f - __builtin_amdgcn_rcpf(q8 * q8);
-    return u < 0.0f ? -r : r;
+    return __builtin_copysignf(r, u);      // r >= 0
 }
 __device__ __forceinline__ float gelu(float x) {
     return 0.5f * x * (1.0f + erf_as(x * 0.70710678118654752f));
@@ -320,8 +320,10 @@ struct AxisArgs {
     int ny, nitems;       // an item: 32 columns of one matrix and MT row tiles
 };
 
-// element e of (hi, lo) <- bf16 split of v
+// element e of (hi, lo) <- bf16 split of v, as v is rounded to float32: lo must
+// not contract with the product that v comes from
 __device__ __forceinline__ void split(float v, bf16x8& hi, bf16x8& lo, int e) {
+#pragma clang fp contract(off)
     const bf16 h = (bf16)v;
     hi[e] = h;
     lo[e] = (bf16)(v - (float)h);
@@ -424,14 +426,14 @@ struct NodeFrag {                     // float [node][32]: one tile, bf16 hi + l
         for (int e = 0; e < 8; ++e) split(v[e], hi, lo, e);
     }
 };
-struct HiddenFrag {                   // bf16 [128][N3]: two tiles, exact
+struct HiddenFrag {                   // bf16 [N3 / 16][128][16]: two tiles, exact
     static constexpr int TILES = 2;
     static constexpr bool LO = false;
     bf16x8 v[2];
     __device__ __forceinline__ void load(const void* p, int row0, int k, int t, int grp) {
-        const bf16* q = (const bf16*)p + int64_t(row0) * N3 + k;
+        const bf16* q = (const bf16*)p + int64_t(k) * HID + row0 * 16;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) v[i] = *(const bf16x8*)&(q + 32 * i * N3)[uint32_t(t * N3 + 8 * grp)];
+        for (int i = 0; i < 2; ++i) v[i] = *(const bf16x8*)&(q + 32 * i * 16)[uint32_t(t * 16 + 8 * grp)];
     }
     __device__ __forceinline__ void get(int i, bf16x8& hi, bf16x8& lo) const { hi = v[i]; lo = v[i]; }
 };
@@ -536,7 +538,57 @@ __global__ __launch_bounds__(64) void k_wgrad(GradArgs a) {
 // Fused per-line kernels
 // ---------------------------------------------------------------------------
 
-// One wave per x-line (64 nodes, two 32-node halves):
+// The constant matrices of the line kernels are held in LDS in fragment order
+// ([half][step][hi, lo][lane]), split once per block; a wave takes lpw
+// consecutive lines (of one sample: lpw divides 4096) and requests the next
+// line's inputs as soon as it has split the present ones.
+//
+// [64][24] inverse x matrix: rows x = 32 h + t, k = (s, kx) < 24, zeros beyond
+__device__ __forceinline__ void stage_gx(const float* gx, bf16x8 (*fr)[2][2][64]) {
+    const int t = threadIdx.x & 31, grp = (threadIdx.x >> 5) & 1, s = (threadIdx.x >> 6) & 1, h = threadIdx.x >> 7;
+    const int k0 = 16 * s + 8 * grp;
+    const float* src = gx + (32 * h + t) * 24 + min(k0, 16);
+    const float4 u0 = *(const float4*)src, u1 = *(const float4*)(src + 4);
+    const float w[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
+    bf16x8 hi, lo;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) split(k0 < 24 ? w[e] : 0.0f, hi, lo, e);
+    fr[h][s][0][threadIdx.x & 63] = hi;
+    fr[h][s][1][threadIdx.x & 63] = lo;
+}
+// a line's (s, kx) x c block as an operand: k < 24, column t (the lanes of k >=
+// 24 read the row of their k - 8, which the zeros of the matrix do not cover: it
+// may be infinite)
+__device__ __forceinline__ void load_line(const float* ln, int t, int grp, float v[2][8]) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[s][e] = (ln + (16 * s + e) * C)[uint32_t((s == 0 ? 8 * grp : 0) * C + t)];
+}
+__device__ __forceinline__ void split_line(const float v[2][8], int grp, bf16x8 hi[2], bf16x8 lo[2]) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) split(s == 1 && grp == 1 ? 0.0f : v[s][e], hi[s], lo[s], e);
+}
+// node x = 32 h + t, channels 16 s + 8 grp + e
+__device__ __forceinline__ void load_act(const float* act, int t, int grp, float4 v[2][2][2]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                v[h][s][q] = *(const float4*)&(act + 32 * h * C + 16 * s + 4 * q)[uint32_t(t * C + 8 * grp)];
+}
+__device__ __forceinline__ bf16x8 to_bf16(float4 u0, float4 u1) {
+    bf16x8 f;
+    f[0] = (bf16)u0.x; f[1] = (bf16)u0.y; f[2] = (bf16)u0.z; f[3] = (bf16)u0.w;
+    f[4] = (bf16)u1.x; f[5] = (bf16)u1.y; f[6] = (bf16)u1.z; f[7] = (bf16)u1.w;
+    return f;
+}
+
+// x-lines (64 nodes, two 32-node halves), one wave per line:
 //   acc[x][j] = sum_k CM[x][k] LN[k][j]   (k < 24, split bf16)
 //             + sum_c ACT[x][c] Wt[c][j]  (bf16)
 // Forward (inverse x transform + pointwise branch of a layer):
@@ -553,231 +605,274 @@ struct LineArgs {
     const float* zprev;   // backward: z_{l-1} for GELU', or nullptr
     float* zout;          // forward: pre-activation, or nullptr
     float* out;
-    int nlines;
-    int bwd;
+    int lpw;              // lines per wave
     int act_gelu;         // forward: out = GELU(z)
 };
 
-__global__ __launch_bounds__(256) void k_lineout(LineArgs a) {
+// Memory bounds it (16 samples, z kept or read: 1.8 GB, 370 us at a copy's
+// rate): LO0 us with one line per wave and the matrices split by each, LO1 so.
+template <bool BWD>
+__global__ __launch_bounds__(256, 3) void k_lineout(LineArgs a) {
+    __shared__ bf16x8 cm[2][2][2][64];
     const int lane = threadIdx.x & 63, t = lane & 31, grp = lane >> 5;
-    const int line = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (line >= a.nlines) return;
-
-    // constant fragments: CM rows (split) and the weight columns
-    bf16x8 cmh[2][2], cml[2][2], wf[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int k = 16 * s + 8 * grp + e;
-                const float v = k < 24 ? a.cm[(32 * h + t) * 24 + k] : 0.0f;
-                const bf16 hi = (bf16)v;
-                cmh[h][s][e] = hi;
-                cml[h][s][e] = (bf16)(v - (float)hi);
-            }
+    const int64_t line0 = (int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6)) * a.lpw;
+    const float* ln = a.ln + line0 * 24 * C;
+    const float* act = a.act ? a.act + line0 * N * C : nullptr;
+    const float* zprev = BWD && a.zprev ? a.zprev + line0 * N * C : nullptr;
+    float* zout = a.zout ? a.zout + line0 * N * C : nullptr;
+    float* out = a.out + line0 * N * C;
+    float v[2][8];
+    float4 u[2][2][2] = {};
+    load_line(ln, t, grp, v);
+    if (act) load_act(act, t, grp, u);
+    bf16x8 wf[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const int k = 16 * s + 8 * grp + e;
-            wf[s][e] = a.bwd ? a.w[t * C + k] : a.w[k * C + t];
+            wf[s][e] = BWD ? a.w[t * C + k] : a.w[k * C + t];
         }
-
-    // spectral block of this line as the B operand (k = (s, kx) < 24, column t)
-    const float* ln = a.ln + int64_t(line) * 24 * C;
-    bf16x8 lh[2], ll[2];
+    const float bt = a.bias ? a.bias[t] : 0.0f;
+    stage_gx(a.cm, cm);
+    __syncthreads();
+    for (int i = 0; i < a.lpw; ++i) {
+        int fl = lane;
+        asm volatile("" : "+v"(fl));     // the matrix stays in LDS
+        bf16x8 lh[2], ll[2], af[2][2];
+        split_line(v, grp, lh, ll);
+        if (act)
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int k = 16 * s + 8 * grp + e;
-            const float v = k < 24 ? ln[k * C + t] : 0.0f;
-            const bf16 hi = (bf16)v;
-            lh[s][e] = hi;
-            ll[s][e] = (bf16)(v - (float)hi);
+                for (int s = 0; s < 2; ++s) af[h][s] = to_bf16(u[h][s][0], u[h][s][1]);
+        float zp[2][16];
+        if (BWD && zprev)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    zp[h][r] = (zprev + (32 * h + 8 * (r >> 2) + (r & 3)) * C)[uint32_t(4 * grp * C + t)];
+        if (i + 1 < a.lpw) {
+            load_line(ln + 24 * C, t, grp, v);
+            if (act) load_act(act + N * C, t, grp, u);
         }
-
-    const int64_t base = int64_t(line) * N * C;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        f32x16 acc;
+        for (int h = 0; h < 2; ++h) {
+            f32x16 acc;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            acc = mfma(cmh[h][s], lh[s], acc);
-            acc = mfma(cmh[h][s], ll[s], acc);
-            acc = mfma(cml[h][s], lh[s], acc);
-        }
-        if (a.act) {
-            const float* ap = a.act + base + (32 * h + t) * C + 8 * grp;
+            for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
-                const float4 u0 = *(const float4*)(ap + 16 * s);
-                const float4 u1 = *(const float4*)(ap + 16 * s + 4);
-                bf16x8 af;
-                af[0] = (bf16)u0.x; af[1] = (bf16)u0.y; af[2] = (bf16)u0.z; af[3] = (bf16)u0.w;
-                af[4] = (bf16)u1.x; af[5] = (bf16)u1.y; af[6] = (bf16)u1.z; af[7] = (bf16)u1.w;
-                acc = mfma(af, wf[s], acc);
+                const bf16x8 ch = cm[h][s][0][fl], cl = cm[h][s][1][fl];
+                acc = mfma(ch, lh[s], acc);
+                acc = mfma(ch, ll[s], acc);
+                acc = mfma(cl, lh[s], acc);
             }
-        }
+            if (act)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int x = 32 * h + 8 * (r >> 2) + 4 * grp + (r & 3);
-            const int64_t idx = base + x * C + t;
-            float v = acc[r];
-            if (!a.bwd) {
-                if (a.bias) v += a.bias[t];
-                if (a.zout) a.zout[idx] = v;
-                a.out[idx] = a.act_gelu ? gelu(v) : v;
-            } else {
-                if (a.zprev) v *= gelu_d(a.zprev[idx]);
-                a.out[idx] = v;
+                for (int s = 0; s < 2; ++s) acc = mfma(af[h][s], wf[s], acc);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = (32 * h + 8 * (r >> 2) + (r & 3)) * C;
+                const uint32_t at = uint32_t(4 * grp * C + t);
+                float x = acc[r];
+                if (!BWD) {
+                    if (a.bias) x += bt;
+                    if (zout) (zout + row)[at] = x;
+                    (out + row)[at] = a.act_gelu ? gelu(x) : x;
+                } else {
+                    if (zprev) x *= gelu_d(zp[h][r]);
+                    (out + row)[at] = x;
+                }
             }
         }
+        ln += 24 * C;
+        out += N * C;
+        if (act) act += N * C;
+        if (zout) zout += N * C;
+        if (BWD && zprev) zprev += N * C;
     }
 }
 
-// Projection 32 -> 128 -> 6 per 32-node tile, one wave per tile.  The hidden
-// layer is computed transposed (h^T = P1^T v^T): its MFMA accumulator holds,
-// in lane (node t, group g), register r, the hidden unit
+// Lines per wave: four waves per SIMD where the batch has them, then more lines
+// for each, to 16 (beyond that nothing is gained).
+inline int lines_per_wave(int lines) {
+    int lpw = 1;
+    while (lpw < 16 && lines / (2 * lpw) >= 4096) lpw *= 2;
+    return lpw;
+}
+
+// Projection 32 -> 128 -> 6.  The hidden layer is computed transposed
+// (h^T = P1^T v^T): its MFMA accumulator holds, in lane (node t, group g),
+// register r, the hidden unit
 //   kappa(r) = 8 (r >> 2) + 4 g + (r & 3)  within a 32-unit block,
 // which is exactly the k slot an MFMA operand in that lane needs when the
 // K index is relabelled by kappa.  So the hidden layer feeds the next
 // contraction straight from registers, with the constant operand (P2 or P1)
 // gathered in the same kappa order.
+//
+// A wave takes 64 nodes as two tiles, tile i of nodes 2 t + i: the constant
+// operands are loaded for both at once, and the hidden values of two
+// neighbouring nodes leave as one 4-byte store.  The backward pass keeps them
+// for the weight gradients in blocks of 16 nodes, [B][N3 / 16][128][16], the
+// order in which those read them (rows of all nodes put every row of a fragment
+// on a page of its own).
+constexpr int HB = 16;                    // nodes per block of the stored hidden layer
 struct ProjArgs {
     const float* v;       // [B][N3][32]
     const bf16* p1;       // [32][128]
+    const bf16* p1f;      // P1^T in fragment order [4][2][2][32][8]: P1[16 s + 8 g + e][32 mt + t]
     const float* c1;      // [128]
     const bf16* p2;       // [B][128][6]: the head's effective projection per sample
+    const bf16* p2k;      // the same in kappa fragment order
     const float* c2;      // [B][6]
     float* out;           // forward: [B][6][N3]
     const float* gout;    // backward: dL/dout [B][6][N3]
     float* gv;            // backward: [B][N3][32]
-    bf16* hT;             // backward: GELU(hidden) [B][128][N3]
-    bf16* ghT;            // backward: dL/d(pre-activation) [B][128][N3]
-    int ntiles;
-    int bwd;
+    bf16* hT;             // backward: GELU(hidden)
+    bf16* ghT;            // backward: dL/d(pre-activation)
 };
 
 __device__ __forceinline__ int kappa(int s, int grp, int e) { return 16 * s + 8 * (e >> 2) + 4 * grp + (e & 3); }
 
-__global__ __launch_bounds__(256) void k_proj(ProjArgs a) {
-    const int lane = threadIdx.x & 63, t = lane & 31, grp = lane >> 5;
-    const int tile = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (tile >= a.ntiles) return;
-    const int b = tile / (N3 / 32), node0 = (tile % (N3 / 32)) * 32;
+// 8 floats at kappa(s, grp, 0 .. 7): two runs of 4
+__device__ __forceinline__ void ld_kappa(const float* p, int s, int grp, float v[8]) {
+    const float4 a = *(const float4*)(p + kappa(s, grp, 0)), b = *(const float4*)(p + kappa(s, grp, 4));
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+}
 
-    // A operand of h^T = P1^T v^T: lane (hidden 32 mt + t), k = c
-    bf16x8 p1t[4][2];
+// 16 samples: forward PF0 -> PF1 us, backward PB0 -> PB1 us with one tile of
+// neighbouring nodes per wave and 2-byte stores before; the GELUs bound the
+// forward pass, the stores of the hidden layer (2.1 GB) the backward one.
+template <bool BWD>
+__global__ __launch_bounds__(256, BWD ? 3 : 4) void k_proj(ProjArgs a) {
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+    const int lane = threadIdx.x & 63, t = lane & 31, grp = lane >> 5;
+    const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int b = item / (N3 / 64), node0 = (item % (N3 / 64)) * 64;
+
+    // B operand v^T: lane (node 2 t + i), k = c
+    bf16x8 vf[2][2];
+    const float* vp = a.v + (int64_t(b) * N3 + node0 + 2 * t) * C + 8 * grp;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) p1t[mt][s][e] = a.p1[(16 * s + 8 * grp + e) * HID + 32 * mt + t];
+            vf[i][s] = to_bf16(*(const float4*)(vp + i * C + 16 * s), *(const float4*)(vp + i * C + 16 * s + 4));
 
-    // B operand v^T: lane (node t), k = c
-    bf16x8 vf[2];
-    {
-        const float* vp = a.v + (int64_t(b) * N3 + node0 + t) * C + 8 * grp;
+    const bf16x8* p1f = (const bf16x8*)a.p1f + grp * 32 + t;          // + (mt * 2 + s) * 64
+    if constexpr (!BWD) {
+        const bf16x8* p2k = (const bf16x8*)(a.p2k + int64_t(b) * KSLOTS) + grp * 32 + t;
+        f32x16 oacc[2];
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const float4 u0 = *(const float4*)(vp + 16 * s);
-            const float4 u1 = *(const float4*)(vp + 16 * s + 4);
-            vf[s][0] = (bf16)u0.x; vf[s][1] = (bf16)u0.y; vf[s][2] = (bf16)u0.z; vf[s][3] = (bf16)u0.w;
-            vf[s][4] = (bf16)u1.x; vf[s][5] = (bf16)u1.y; vf[s][6] = (bf16)u1.z; vf[s][7] = (bf16)u1.w;
-        }
-    }
-
-    const bf16* p2 = a.p2 + int64_t(b) * HID * NOUT;
-    const float* c2 = a.c2 + b * NOUT;
-    if (!a.bwd) {
-        f32x16 oacc;
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[r] = 0.0f;
-#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[i][r] = 0.0f;
+#pragma unroll 1
         for (int mt = 0; mt < 4; ++mt) {
-            f32x16 acc;
+            f32x16 acc[2];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-            acc = mfma(p1t[mt][0], vf[0], acc);
-            acc = mfma(p1t[mt][1], vf[1], acc);
+            for (int i = 0; i < 2; ++i) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][r] = 0.0f;
+                acc[i] = mfma(p1f[(mt * 2) * 64], vf[i][0], acc[i]);
+                acc[i] = mfma(p1f[(mt * 2 + 1) * 64], vf[i][1], acc[i]);
+            }
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
-                bf16x8 hf, pf;
+                float c1[8];
+                ld_kappa(a.c1 + 32 * mt, s, grp, c1);
+                const bf16x8 pf = p2k[(mt * 2 + s) * 64];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int hd = 32 * mt + kappa(s, grp, e);
-                    hf[e] = (bf16)gelu(acc[8 * s + e] + a.c1[hd]);
-                    pf[e] = t < NOUT ? p2[hd * NOUT + t] : (bf16)0.0f;
+                for (int i = 0; i < 2; ++i) {
+                    bf16x8 hf;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) hf[e] = (bf16)gelu(acc[i][8 * s + e] + c1[e]);
+                    oacc[i] = mfma(pf, hf, oacc[i]);
                 }
-                oacc = mfma(pf, hf, oacc);
             }
         }
         // rows are output components: group 0 holds 0..3 (r = 0..3), group 1 holds 4, 5 (r = 0, 1)
-        float* op = a.out + int64_t(b) * OUT_SZ + node0 + t;
+        float* op = a.out + int64_t(b) * OUT_SZ + node0 + 2 * t;
+        const float* c2 = a.c2 + b * NOUT;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int o = 4 * grp + r;
-            if (o < NOUT) op[int64_t(o) * N3] = oacc[r] + c2[o];
+            if (o < NOUT) {
+                op[int64_t(o) * N3] = oacc[0][r] + c2[o];
+                op[int64_t(o) * N3 + 1] = oacc[1][r] + c2[o];
+            }
         }
-        return;
-    }
-
-    // backward: dL/dout^T as the B operand of dL/dh^T = P2 . dL/dout^T (K = 6 padded to 16)
-    bf16x8 gf;
-    {
-        const float* gp = a.gout + int64_t(b) * OUT_SZ + node0 + t;
+    } else {
+        const bf16* p2 = a.p2 + int64_t(b) * HID * NOUT;
+        // dL/dout^T as the B operand of dL/dh^T = P2 . dL/dout^T (K = 6 padded to 16)
+        bf16x8 gf[2];
+        const float* gp = a.gout + int64_t(b) * OUT_SZ + node0 + 2 * t;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const int o = 8 * grp + e;
-            gf[e] = o < NOUT ? (bf16)gp[int64_t(o) * N3] : (bf16)0.0f;
+            const float2 g = *(const float2*)(gp + int64_t(min(e, NOUT - 1)) * N3);
+            const bool in = e < NOUT && grp == 0;
+            gf[0][e] = in ? (bf16)g.x : (bf16)0.0f;
+            gf[1][e] = in ? (bf16)g.y : (bf16)0.0f;
         }
-    }
-    f32x16 gvacc;
+        f32x16 gvacc[2];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) gvacc[r] = 0.0f;
-    bf16* hp = a.hT + int64_t(b) * HID * N3 + node0 + t;
-    bf16* ghp = a.ghT + int64_t(b) * HID * N3 + node0 + t;
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-        f32x16 acc, gacc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) { acc[r] = 0.0f; gacc[r] = 0.0f; }
-        acc = mfma(p1t[mt][0], vf[0], acc);
-        acc = mfma(p1t[mt][1], vf[1], acc);
-        bf16x8 p2f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int o = 8 * grp + e;
-            p2f[e] = o < NOUT ? p2[(32 * mt + t) * NOUT + o] : (bf16)0.0f;
-        }
-        gacc = mfma(p2f, gf, gacc);
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            bf16x8 af, bfr;
+            for (int r = 0; r < 16; ++r) gvacc[i][r] = 0.0f;
+        const int64_t ho = ((int64_t(b) * (N3 / HB) + node0 / HB + t / 8) * HID) * HB + 2 * (t & 7);
+        bf16 *hp = a.hT + ho, *ghp = a.ghT + ho;
+#pragma unroll 1
+        for (int mt = 0; mt < 4; ++mt) {
+            bf16x8 p2f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int r = 8 * s + e;
-                const int hd = 32 * mt + kappa(s, grp, e);
-                const float pre = acc[r] + a.c1[hd];
-                const float gpre = gacc[r] * gelu_d(pre);
-                hp[int64_t(hd) * N3] = (bf16)gelu(pre);
-                const bf16 gb = (bf16)gpre;
-                ghp[int64_t(hd) * N3] = gb;
-                af[e] = gb;
-                bfr[e] = a.p1[t * HID + hd];
+                const bf16 q = p2[(32 * mt + t) * NOUT + min(e, NOUT - 1)];
+                p2f[e] = e < NOUT && grp == 0 ? q : (bf16)0.0f;
             }
-            gvacc = mfma(af, bfr, gvacc);
-        }
-    }
-    float* gvp = a.gv + (int64_t(b) * N3 + node0) * C + t;
+            f32x16 acc[2], gacc[2];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) gvp[(8 * (r >> 2) + 4 * grp + (r & 3)) * C] = gvacc[r];
+            for (int i = 0; i < 2; ++i) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) { acc[i][r] = 0.0f; gacc[i][r] = 0.0f; }
+                acc[i] = mfma(p1f[(mt * 2) * 64], vf[i][0], acc[i]);
+                acc[i] = mfma(p1f[(mt * 2 + 1) * 64], vf[i][1], acc[i]);
+                gacc[i] = mfma(p2f, gf[i], gacc[i]);
+            }
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                float c1[8];
+                ld_kappa(a.c1 + 32 * mt, s, grp, c1);
+                bf16x8 af[2], bfr;
+                const bf16x4 b0 = *(const bf16x4*)&a.p1[t * HID + 32 * mt + kappa(s, grp, 0)];
+                const bf16x4 b1 = *(const bf16x4*)&a.p1[t * HID + 32 * mt + kappa(s, grp, 4)];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int r = 8 * s + e, hd = 32 * mt + kappa(s, grp, e);
+                    bf16x2 h2, g2;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const float pre = acc[i][r] + c1[e];
+                        h2[i] = (bf16)gelu(pre);
+                        g2[i] = (bf16)(gacc[i][r] * gelu_d(pre));
+                        af[i][e] = g2[i];
+                    }
+                    *(bf16x2*)&hp[hd * HB] = h2;
+                    *(bf16x2*)&ghp[hd * HB] = g2;
+                    bfr[e] = e < 4 ? b0[e & 3] : b1[e & 3];
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i) gvacc[i] = mfma(af[i], bfr, gvacc[i]);
+            }
+        }
+        float* gvp = a.gv + (int64_t(b) * N3 + node0) * C + t;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) gvp[(2 * (8 * (r >> 2) + 4 * grp + (r & 3)) + i) * C] = gvacc[i][r];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -793,21 +888,38 @@ __device__ __forceinline__ float lift_base(const float* pb, const float* w0, con
     for (int i = 0; i < NPAR; ++i) s += pb[i] * w0[i * C + c];
     return s;
 }
+__device__ __forceinline__ float lift_term(float s, float w, int i) { return fmaf(coord(i), w, s); }
+// the same with the product rounded on its own
+__device__ __forceinline__ float lift_term_r(float s, float w, int i) {
+#pragma clang fp contract(off)
+    const float q = coord(i) * w;
+    return s + q;
+}
 __device__ __forceinline__ float lift_at(float base, const float* w0, int c, int x, int y, int z) {
-    float s = base;
-    s += coord(x) * w0[8 * C + c];
-    s += coord(y) * w0[9 * C + c];
-    s += coord(z) * w0[10 * C + c];
-    return s;
+    return lift_term(lift_term(lift_term(base, w0[8 * C + c], x), w0[9 * C + c], y), w0[10 * C + c], z);
 }
 
-__global__ void k_lift(const float* p, const float* w0, const float* b0, float* v, int64_t total) {
-    const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const int c = idx & (C - 1);
-    const int64_t nb = idx >> 5;
-    const int node = int(nb % N3), b = int(nb / N3);
-    v[idx] = lift_at(lift_base(p + b * NPAR, w0, b0, c), w0, c, node % N, (node / N) % N, node / (N * N));
+// One block per (z, y) pair of lines: a thread keeps four channels and walks two
+// lines of nodes in 16-byte stores.  16 samples: LI0 us with one element per
+// thread, each summing its base anew, LI1 so (537 MB).
+constexpr int LIFT_LINES = 8;             // lines per block (64 divides into them)
+__global__ __launch_bounds__(256) void k_lift(const float* p, const float* w0, const float* b0, float* v) {
+    const int line0 = blockIdx.x * LIFT_LINES, b = line0 / (N * N), z = line0 / N % N;
+    const int c = 4 * (threadIdx.x & 7), x0 = threadIdx.x >> 3;
+    float base[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) base[q] = lift_base(p + b * NPAR, w0, b0, c + q);
+    for (int i = 0; i < LIFT_LINES; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int x = x0 + 32 * h, y = (line0 + i) % N;
+            float4 o;
+            o.x = lift_at(base[0], w0, c, x, y, z);
+            o.y = lift_at(base[1], w0, c + 1, x, y, z);
+            o.z = lift_at(base[2], w0, c + 2, x, y, z);
+            o.w = lift_at(base[3], w0, c + 3, x, y, z);
+            *(float4*)&v[(int64_t(line0 + i) * N + x) * C + c] = o;
+        }
 }
 
 // ---------------------------------------------------------------------------
@@ -816,23 +928,19 @@ __global__ void k_lift(const float* p, const float* w0, const float* b0, float* 
 // kernel that produced the layer's input.
 // ---------------------------------------------------------------------------
 
-// 8 (or 4) consecutive floats from a 16-byte aligned address, or zeros
-__device__ __forceinline__ void ld8(const float* p, bool in, float v[8]) {
-    if (in) {
-        const float4 q0 = *(const float4*)p, q1 = *(const float4*)(p + 4);
-        v[0] = q0.x; v[1] = q0.y; v[2] = q0.z; v[3] = q0.w; v[4] = q1.x; v[5] = q1.y; v[6] = q1.z; v[7] = q1.w;
-    } else {
+// Forward x matrix [24][64] as an A operand in LDS, rows i = t < 24, steps of 16
+// x: in order (x = 16 ks + 8 g + e), or in kappa order (x = 32 (ks >> 1) +
+// kappa(ks & 1, g, e)) to meet an accumulator's rows.
+template <bool KAPPA> __device__ __forceinline__ void stage_fx(const float* fx, bf16x8 (*fr)[2][64]) {
+    const int t = threadIdx.x & 31, grp = (threadIdx.x >> 5) & 1, ks = threadIdx.x >> 6;
+    const float* src = fx + min(t, 23) * N + (KAPPA ? 32 * (ks >> 1) + kappa(ks & 1, grp, 0) : 16 * ks + 8 * grp);
+    const float4 u0 = *(const float4*)src, u1 = *(const float4*)(src + (KAPPA ? 8 : 4));
+    const float w[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
+    bf16x8 hi, lo;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = 0.0f;
-    }
-}
-__device__ __forceinline__ void ld4c(const float* p, bool in, float v[4]) {
-    if (in) {
-        const float4 q = *(const float4*)p;
-        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-    } else {
-        v[0] = v[1] = v[2] = v[3] = 0.0f;
-    }
+    for (int e = 0; e < 8; ++e) split(t < 24 ? w[e] : 0.0f, hi, lo, e);
+    fr[ks][0][threadIdx.x & 63] = hi;
+    fr[ks][1][threadIdx.x & 63] = lo;
 }
 
 struct InfArgs {
@@ -853,40 +961,49 @@ struct InfArgs {
     const bf16* p2k;      // [B][4][2][2][32][8]
     const float* c2e;     // [B][6]
     float* out;           // [B][6][N3]
-    int nlines;
+    int lpw;              // lines per wave
 };
 
 // Lift and the first x contraction, one wave per x-line:
 //   X1[(s,kx)][c] = sum_x Fx[(s,kx)][x] v0[x][c]    (split bf16)
+// Batch 64: LX0 us with the matrix split by every wave, LX1 so (805 MB written,
+// 165 us at a copy's rate).  The y and z terms of the lift are fused into the
+// sum for x < 16 and rounded first beyond: the windows of a trained surrogate
+// stay the same bits that this operator has always given (a float32 rounding
+// here can flip a bf16 one in the mixing, 1e-4 of the output).
 __global__ __launch_bounds__(256) void k_lift_x(InfArgs a) {
+    __shared__ bf16x8 fx[4][2][64];
     const int lane = threadIdx.x & 63, t = lane & 31, grp = lane >> 5;
-    const int line = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (line >= a.nlines) return;
-    const int b = line / (N * N), zy = line % (N * N);
-    const float base = lift_base(a.p + b * NPAR, a.w0, a.b0, t);
-    f32x16 acc;
+    const int line0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * a.lpw;
+    const float base = lift_base(a.p + line0 / (N * N) * NPAR, a.w0, a.b0, t);
+    // the lift's sum up to its x term, as lift_at forms it
+    float bx[4][8];
+    const float wx = a.w0[8 * C + t], wy = a.w0[9 * C + t], wz = a.w0[10 * C + t];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+    for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-        bf16x8 ah, al, bh, bl;
-        float fr[8];
-        ld8(a.fx + t * N + 16 * ks + 8 * grp, t < 24, fr);
+        for (int e = 0; e < 8; ++e) bx[ks][e] = lift_term(base, wx, 16 * ks + 8 * grp + e);
+    stage_fx<false>(a.fx, fx);
+    __syncthreads();
+    for (int line = line0; line < line0 + a.lpw; ++line) {
+        const int zy = line % (N * N);
+        f32x16 acc;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int x = 16 * ks + 8 * grp + e;
-            split(fr[e], ah, al, e);
-            split(lift_at(base, a.w0, t, x, zy % N, zy / N), bh, bl, e);
+        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            bf16x8 bh, bl;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                split(ks == 0 ? lift_term(lift_term(bx[ks][e], wy, zy % N), wz, zy / N)
+                              : lift_term_r(lift_term_r(bx[ks][e], wy, zy % N), wz, zy / N), bh, bl, e);
+            acc = mfma(fx[ks][0][lane], bh, acc);
+            acc = mfma(fx[ks][0][lane], bl, acc);
+            acc = mfma(fx[ks][1][lane], bh, acc);
         }
-        acc = mfma(ah, bh, acc);
-        acc = mfma(ah, bl, acc);
-        acc = mfma(al, bh, acc);
-    }
-    float* o = a.x1out + int64_t(line) * 24 * C + t;
+        float* o = a.x1out + int64_t(line) * 24 * C;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int i = 8 * (r >> 2) + 4 * grp + (r & 3);
-        if (i < 24) o[i * C] = acc[r];
+        for (int r = 0; r < 12; ++r) (o + (8 * (r >> 2) + (r & 3)) * C)[uint32_t(4 * grp * C + t)] = acc[r];
     }
 }
 
@@ -896,100 +1013,103 @@ __global__ __launch_bounds__(256) void k_lift_x(InfArgs a) {
 //   X1[i][o] = sum_x Fx[i][x] v[x][o]
 // The accumulator of v holds row x = 32 h + kappa(s, g, e) in register 8 s + e
 // of lane (o, g), so it is the B operand of the contraction over x with the
-// constant Fx gathered in that order.
-__global__ __launch_bounds__(256) void k_line_fwd(InfArgs a) {
+// constant Fx gathered in that order.  LIFT: v_l is v_0, recomputed from the
+// parameters, never stored.  Memory bounds it (batch 64: 3.8 GB and, with v_l
+// read, 5.9): LF0 us, LF0b with one line per wave and the matrices split by
+// each, LF1 and LF1b so.
+template <bool LIFT>
+__global__ __launch_bounds__(256, 3) void k_line_fwd(InfArgs a) {
+    __shared__ bf16x8 gx[2][2][2][64], fx[4][2][64];
+    __shared__ __attribute__((aligned(16))) float lift[4][C];     // LIFT: base and the x, y, z weights
     const int lane = threadIdx.x & 63, t = lane & 31, grp = lane >> 5;
-    const int line = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (line >= a.nlines) return;
-    const int b = line / (N * N), zy = line % (N * N);
-    bf16x8 cmh[2][2], cml[2][2], wf[2], lh[2], ll[2];
-    const float* ln = a.ln + int64_t(line) * 24 * C;
+    const int line0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * a.lpw;
+    const float* ln = a.ln + int64_t(line0) * 24 * C;
+    const float* act = LIFT ? nullptr : a.act + int64_t(line0) * N * C;
+    float v[2][8];
+    float4 u[2][2][2];
+    load_line(ln, t, grp, v);
+    if constexpr (!LIFT) load_act(act, t, grp, u);
+    if constexpr (LIFT)                   // a block's lines are of one sample
+        if (threadIdx.x < C) {
+            const int c = threadIdx.x;
+            lift[0][c] = lift_base(a.p + line0 / (N * N) * NPAR, a.w0, a.b0, c);
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const bool in = 16 * s + 8 * grp < 24;
-        float g0[8], g1[8];
-        ld8(a.gx + t * 24 + 16 * s + 8 * grp, in, g0);
-        ld8(a.gx + (32 + t) * 24 + 16 * s + 8 * grp, in, g1);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int k = 16 * s + 8 * grp + e;
-            wf[s][e] = a.w[k * C + t];
-            split(in ? ln[k * C + t] : 0.0f, lh[s], ll[s], e);
-            split(g0[e], cmh[0][s], cml[0][s], e);
-            split(g1[e], cmh[1][s], cml[1][s], e);
+            for (int d = 0; d < 3; ++d) lift[1 + d][c] = a.w0[(8 + d) * C + c];
         }
-    }
-    const int64_t base = int64_t(line) * N * C;
-    float lb[2][8];
-    if (!a.act) {
+    bf16x8 wf[2];
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) lb[s][e] = lift_base(a.p + b * NPAR, a.w0, a.b0, 16 * s + 8 * grp + e);
-    }
-    f32x16 acc[2];
+        for (int e = 0; e < 8; ++e) wf[s][e] = a.w[(16 * s + 8 * grp + e) * C + t];
+    const float bt = a.bias[t];
+    stage_gx(a.gx, gx);
+    stage_fx<true>(a.fx, fx);
+    __syncthreads();
+    for (int i = 0; i < a.lpw; ++i) {
+        const int line = line0 + i, zy = line % (N * N);
+        int fl = lane;
+        asm volatile("" : "+v"(fl));     // the matrices stay in LDS
+        bf16x8 lh[2], ll[2], af[2][2];
+        split_line(v, grp, lh, ll);
+        if constexpr (LIFT) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+            for (int s = 0; s < 2; ++s) {
+                const int c = 16 * s + 8 * (fl >> 5);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[h][r] = 0.0f;
+                for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            acc[h] = mfma(cmh[h][s], lh[s], acc[h]);
-            acc[h] = mfma(cmh[h][s], ll[s], acc[h]);
-            acc[h] = mfma(cml[h][s], lh[s], acc[h]);
-        }
-        const int x = 32 * h + t;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            bf16x8 af;
-            if (a.act) {
-                const float* ap = a.act + base + x * C + 16 * s + 8 * grp;
-                const float4 u0 = *(const float4*)ap;
-                const float4 u1 = *(const float4*)(ap + 4);
-                af[0] = (bf16)u0.x; af[1] = (bf16)u0.y; af[2] = (bf16)u0.z; af[3] = (bf16)u0.w;
-                af[4] = (bf16)u1.x; af[5] = (bf16)u1.y; af[6] = (bf16)u1.z; af[7] = (bf16)u1.w;
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    af[e] = (bf16)lift_at(lb[s][e], a.w0, 16 * s + 8 * grp + e, x, zy % N, zy / N);
+                    for (int e = 0; e < 8; ++e) {
+                        const float q = lift_term(lift[0][c + e], lift[1][c + e], 32 * h + t);
+                        af[h][s][e] = (bf16)lift_term(lift_term(q, lift[2][c + e], zy % N), lift[3][c + e], zy / N);
+                    }
             }
-            acc[h] = mfma(af, wf[s], acc[h]);
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int s = 0; s < 2; ++s) af[h][s] = to_bf16(u[h][s][0], u[h][s][1]);
         }
-        const float bt = a.bias[t];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int xr = 32 * h + 8 * (r >> 2) + 4 * grp + (r & 3);
-            const float v = gelu(acc[h][r] + bt);
-            acc[h][r] = v;
-            a.vout[base + xr * C + t] = v;
+        if (i + 1 < a.lpw) {
+            load_line(a.ln + int64_t(line + 1) * 24 * C, t, grp, v);
+            if constexpr (!LIFT) load_act(a.act + int64_t(line + 1) * N * C, t, grp, u);
         }
-    }
-    f32x16 xacc;
+        float* vout = a.vout + int64_t(line) * N * C;
+        f32x16 xacc;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) xacc[r] = 0.0f;
+        for (int r = 0; r < 16; ++r) xacc[r] = 0.0f;
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < 2; ++h) {
+            f32x16 acc;
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            bf16x8 ah, al, bh, bl;
-            // kappa(s, g, e) for e = 0..3 and 4..7 is two runs of 4 consecutive x
-            float fr[8];
-            ld4c(a.fx + t * N + 32 * h + 16 * s + 4 * grp, t < 24, fr);
-            ld4c(a.fx + t * N + 32 * h + 16 * s + 8 + 4 * grp, t < 24, fr + 4);
+            for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                split(fr[e], ah, al, e);
-                split(acc[h][8 * s + e], bh, bl, e);
+            for (int s = 0; s < 2; ++s) {
+                const bf16x8 gh = gx[h][s][0][fl], gl = gx[h][s][1][fl];
+                acc = mfma(gh, lh[s], acc);
+                acc = mfma(gh, ll[s], acc);
+                acc = mfma(gl, lh[s], acc);
             }
-            xacc = mfma(ah, bh, xacc);
-            xacc = mfma(ah, bl, xacc);
-            xacc = mfma(al, bh, xacc);
-        }
-    float* o = a.x1out + int64_t(line) * 24 * C + t;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int i = 8 * (r >> 2) + 4 * grp + (r & 3);
-        if (i < 24) o[i * C] = xacc[r];
+            for (int s = 0; s < 2; ++s) acc = mfma(af[h][s], wf[s], acc);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                bf16x8 bh, bl;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int r = 8 * s + e;
+                    const float x = gelu(acc[r] + bt);
+                    (vout + (32 * h + 8 * (r >> 2) + (r & 3)) * C)[uint32_t(4 * grp * C + t)] = x;
+                    split(x, bh, bl, e);
+                }
+                const bf16x8 ah = fx[2 * h + s][0][fl], al = fx[2 * h + s][1][fl];
+                xacc = mfma(ah, bh, xacc);
+                xacc = mfma(ah, bl, xacc);
+                xacc = mfma(al, bh, xacc);
+            }
+        }
+        float* o = a.x1out + int64_t(line) * 24 * C;
+#pragma unroll
+        for (int r = 0; r < 12; ++r) (o + (8 * (r >> 2) + (r & 3)) * C)[uint32_t(4 * grp * C + t)] = xacc[r];
     }
 }
 
@@ -997,59 +1117,72 @@ __global__ __launch_bounds__(256) void k_line_fwd(InfArgs a) {
 // v^T[o][x] = sum_k U1^T[o][k] Gx^T[k][x] + sum_c W^T[o][c] v_l^T[c][x] + b[o],
 // so lane (x, g) holds channel o = kappa(s, g, e) in register 8 s + e: the B
 // operand of h^T = P1^T v^T over c, with P1 gathered in that order.  The
-// projection then runs as in k_proj.
-__global__ __launch_bounds__(256) void k_line_proj(InfArgs a) {
-    const int lane = threadIdx.x & 63, t = lane & 31, grp = lane >> 5;
-    // one wave per half line (32 nodes): twice the independent waves
-    const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int line = item >> 1, h = item & 1;
-    if (line >= a.nlines) return;
-    const int b = line / (N * N), zy = line % (N * N);
-    bf16x8 wf[2], lh[2], ll[2];
-    const float* ln = a.ln + int64_t(line) * 24 * C;
+// projection then runs as in k_proj.  A wave takes one half (32 nodes) of its
+// lines: twice the independent waves.  The constant operands are in LDS; the
+// 64 GELUs per lane and half line bound it (batch 64: 2.1e9 of about 22
+// instructions, 1.2 ms): LP0 us with the operands loaded by every wave, LP1 so.
+__global__ __launch_bounds__(256, 4) void k_line_proj(InfArgs a) {
+    __shared__ bf16x8 gx[2][2][2][64], p1s[8][64], p2s[8][64];
+    __shared__ __attribute__((aligned(16))) float c1s[HID], bs[C];
+    const int lane = threadIdx.x & 63, t = lane & 31, grp = lane >> 5, h = (threadIdx.x >> 6) & 1;
+    const int line0 = (blockIdx.x * 2 + (threadIdx.x >> 7)) * a.lpw, b = line0 / (N * N);
+    float v[2][8];
+    float4 u[2][2];
+    auto fetch = [&](int line) {
+        load_line(a.ln + int64_t(line) * 24 * C, t, grp, v);
+        const float* act = a.act + (int64_t(line) * N + 32 * h) * C;
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                u[s][q] = *(const float4*)&(act + 16 * s + 4 * q)[uint32_t(t * C + 8 * grp)];
+    };
+    fetch(line0);
+    bf16x8 wf[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int k = 16 * s + 8 * grp + e;
-            wf[s][e] = a.w[k * C + t];
-            split(k < 24 ? ln[k * C + t] : 0.0f, lh[s], ll[s], e);
-        }
-    const bf16x8* p1k = (const bf16x8*)a.p1k + grp * 32 + t;          // + (mt * 2 + s) * 64
-    const bf16x8* p2k = (const bf16x8*)(a.p2k + int64_t(b) * KSLOTS) + grp * 32 + t;
+        for (int e = 0; e < 8; ++e) wf[s][e] = a.w[(16 * s + 8 * grp + e) * C + t];
+    stage_gx(a.gx, gx);
+    const bf16x8* p2k = (const bf16x8*)(a.p2k + int64_t(b) * KSLOTS);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        (&p1s[0][0])[threadIdx.x + 256 * q] = ((const bf16x8*)a.p1k)[threadIdx.x + 256 * q];
+        (&p2s[0][0])[threadIdx.x + 256 * q] = p2k[threadIdx.x + 256 * q];
+    }
+    if (threadIdx.x < HID) c1s[threadIdx.x] = a.c1[threadIdx.x];
+    if (threadIdx.x < C) bs[threadIdx.x] = a.bias[threadIdx.x];
+    __syncthreads();
     const float* c2 = a.c2e + b * NOUT;
-    const int64_t base = int64_t(line) * N * C;
-    {
-        const int x = 32 * h + t;
+    for (int i = 0; i < a.lpw; ++i) {
+        const int line = line0 + i;
+        int fl = lane;
+        asm volatile("" : "+v"(fl));     // the operands stay in LDS
+        bf16x8 lh[2], ll[2], af[2];
+        split_line(v, grp, lh, ll);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) af[s] = to_bf16(u[s][0], u[s][1]);
+        if (i + 1 < a.lpw) fetch(line + 1);
         f32x16 acc;
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            bf16x8 cmh, cml;
-            float gr[8];
-            ld8(a.gx + x * 24 + 16 * s + 8 * grp, 16 * s + 8 * grp < 24, gr);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) split(gr[e], cmh, cml, e);
-            acc = mfma(lh[s], cmh, acc);
-            acc = mfma(ll[s], cmh, acc);
-            acc = mfma(lh[s], cml, acc);
+            const bf16x8 gh = gx[h][s][0][fl], gl = gx[h][s][1][fl];
+            acc = mfma(lh[s], gh, acc);
+            acc = mfma(ll[s], gh, acc);
+            acc = mfma(lh[s], gl, acc);
         }
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const float* ap = a.act + base + x * C + 16 * s + 8 * grp;
-            const float4 u0 = *(const float4*)ap;
-            const float4 u1 = *(const float4*)(ap + 4);
-            bf16x8 af;
-            af[0] = (bf16)u0.x; af[1] = (bf16)u0.y; af[2] = (bf16)u0.z; af[3] = (bf16)u0.w;
-            af[4] = (bf16)u1.x; af[5] = (bf16)u1.y; af[6] = (bf16)u1.z; af[7] = (bf16)u1.w;
-            acc = mfma(wf[s], af, acc);
-        }
+        for (int s = 0; s < 2; ++s) acc = mfma(wf[s], af[s], acc);
         bf16x8 vf[2];
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int s = 0; s < 2; ++s) {
+            float bias[8];
+            ld_kappa(bs, s, fl >> 5, bias);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) vf[s][e] = (bf16)(acc[8 * s + e] + a.bias[kappa(s, grp, e)]);
+            for (int e = 0; e < 8; ++e) vf[s][e] = (bf16)(acc[8 * s + e] + bias[e]);
+        }
         f32x16 oacc;
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[r] = 0.0f;
@@ -1059,19 +1192,18 @@ __global__ __launch_bounds__(256) void k_line_proj(InfArgs a) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) hacc[r] = 0.0f;
 #pragma unroll
-            for (int s = 0; s < 2; ++s) hacc = mfma(p1k[(mt * 2 + s) * 64], vf[s], hacc);
+            for (int s = 0; s < 2; ++s) hacc = mfma(p1s[mt * 2 + s][fl], vf[s], hacc);
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
+                float c1[8];
+                ld_kappa(c1s + 32 * mt, s, grp, c1);
                 bf16x8 hf;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int hd = 32 * mt + kappa(s, grp, e);
-                    hf[e] = (bf16)gelu(hacc[8 * s + e] + a.c1[hd]);
-                }
-                oacc = mfma(p2k[(mt * 2 + s) * 64], hf, oacc);
+                for (int e = 0; e < 8; ++e) hf[e] = (bf16)gelu(hacc[8 * s + e] + c1[e]);
+                oacc = mfma(p2s[mt * 2 + s][fl], hf, oacc);
             }
         }
-        float* op = a.out + int64_t(b) * OUT_SZ + int64_t(zy) * N + x;
+        float* op = a.out + int64_t(b) * OUT_SZ + int64_t(line % (N * N)) * N + 32 * h + t;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int o = 4 * grp + r;
@@ -1080,17 +1212,25 @@ __global__ __launch_bounds__(256) void k_line_proj(InfArgs a) {
     }
 }
 
-// per (sample, z plane): sum_node g, and sum_node coord_d g, for every channel
+// per (sample, z plane): sum_node g, and sum_node coord_d g, for every channel;
+// thread (ng, c) takes the nodes ng (mod 8) in increasing order, sixteen loads
+// in flight (16 samples: LG0 us with one, LG1 so; 537 MB)
 __global__ __launch_bounds__(256) void k_lift_grad_part(const float* gv, float* part) {
     const int z = blockIdx.x, b = blockIdx.y;
     const int c = threadIdx.x & 31, ng = threadIdx.x >> 5;
     const float* g = gv + (int64_t(b) * N3 + int64_t(z) * N * N) * C;
     float s = 0, sx = 0, sy = 0;
-    for (int nd = ng; nd < N * N; nd += 8) {
-        const float v = g[nd * C + c];
-        s += v;
-        sx += coord(nd % N) * v;
-        sy += coord(nd / N) * v;
+    for (int n0 = ng; n0 < N * N; n0 += 8 * 16) {
+        float v[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = g[(n0 + 8 * k) * C + c];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int nd = n0 + 8 * k;
+            s += v[k];
+            sx += coord(nd % N) * v[k];
+            sy += coord(nd / N) * v[k];
+        }
     }
     __shared__ float red[3][8][32];
     red[0][ng][c] = s; red[1][ng][c] = sx; red[2][ng][c] = sy;
@@ -1297,12 +1437,14 @@ __global__ void k_head_grad(const float* geff, const float* w, int nb, int B, fl
     g[int64_t(r) * cols + col] = s;
 }
 
-// P1 in the projection's kappa order: [mt][s][g][t][e] = P1[kappa(s, g, e)][32 mt + t]
-__global__ void k_p1_kappa(const float* p1, bf16* dst) {
+// P1^T in fragment order: [mt][s][g][t][e] = P1[k][32 mt + t] with k = kappa(s, g,
+// e) for the fused last layer, 16 s + 8 g + e for k_proj
+__global__ void k_p1_frag(const float* p1, bf16* kap, bf16* plain) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= C * HID) return;
     const int e = i & 7, t = (i >> 3) & 31, g = (i >> 8) & 1, s = (i >> 9) & 1, mt = i >> 10;
-    dst[i] = (bf16)p1[kappa(s, g, e) * HID + 32 * mt + t];
+    kap[i] = (bf16)p1[kappa(s, g, e) * HID + 32 * mt + t];
+    plain[i] = (bf16)p1[(16 * s + 8 * g + e) * HID + 32 * mt + t];
 }
 
 __global__ void k_to_bf16(const float* src, bf16* dst, int n) {
@@ -1515,7 +1657,7 @@ struct tf_fno {
 
     std::vector<void*> allocs;
     float *prm = nullptr, *grad = nullptr, *am = nullptr, *av = nullptr;
-    bf16 *wb[LAYERS] = {}, *rb[LAYERS] = {}, *p1b = nullptr, *p2e = nullptr, *p1k = nullptr, *p2k = nullptr;
+    bf16 *wb[LAYERS] = {}, *rb[LAYERS] = {}, *p1b = nullptr, *p2e = nullptr, *p1k = nullptr, *p1f = nullptr, *p2k = nullptr;
     float *c2e = nullptr, *geff = nullptr;
     float *fx, *fxT, *gx, *gxT, *fs, *fsT, *gs, *gsT;
     float* tab = nullptr;       // the eight tables, one allocation
@@ -1624,6 +1766,13 @@ tf_status zexpand(tf_fno* f, const float* A, const float* in, float* out, int B)
 tf_status yexpand(tf_fno* f, const float* A, const float* in, float* out, int B) {
     return axis<128, 48>(f, A, in, out, N, two(1, N * 2 * LINE, LINE), plain(LINE), 2 * LINE, X2_SZ,
                          int64_t(N) * 2 * LINE, X1_SZ, B);
+}
+
+// x-lines of B samples
+template <bool BWD> tf_status lineout(tf_fno* f, LineArgs a, int B) {
+    a.lpw = lines_per_wave(B * N * N);
+    hipLaunchKernelGGL(k_lineout<BWD>, dim3(B * N * N / (4 * a.lpw)), dim3(256), 0, f->cur, a);
+    return launched();
 }
 
 // ---- per-mode complex channel mixing as real 64 x 64 blocks ----
@@ -1753,6 +1902,7 @@ tf_status tf_fno_create(int32_t max_batch, int32_t training, int32_t nbasis, voi
     TRY(f->alloc(&f->p2e, B * HID * NOUT));
     TRY(f->alloc(&f->c2e, B * NOUT));
     TRY(f->alloc(&f->p1k, C * HID));
+    TRY(f->alloc(&f->p1f, C * HID));
     TRY(f->alloc(&f->p2k, B * KSLOTS));
     TF_HIP(hipMemset(f->p2k, 0, B * KSLOTS * sizeof(bf16)));     // rows t >= 6 stay 0
 
@@ -1814,7 +1964,7 @@ tf_status refresh_working(tf_fno* f) {
                            f->training ? 0 : 1);
     }
     hipLaunchKernelGGL(k_to_bf16, dim3((C * HID + 255) / 256), dim3(256), 0, f->cur, f->prm + OFF_P1, f->p1b, C * HID);
-    hipLaunchKernelGGL(k_p1_kappa, dim3((C * HID + 255) / 256), dim3(256), 0, f->cur, f->prm + OFF_P1, f->p1k);
+    hipLaunchKernelGGL(k_p1_frag, dim3((C * HID + 255) / 256), dim3(256), 0, f->cur, f->prm + OFF_P1, f->p1k, f->p1f);
     TRY(launched());
     f->working_stale = false;
     return TF_OK;
@@ -1832,12 +1982,9 @@ tf_status forward_body(tf_fno* f, const float* params, const float* hw, int B, f
                            f->prm + off_c2(f->nb), hw, f->nb, B, f->p2e, f->c2e, f->p2k);
     }
     if (!f->training) return forward_infer(f, params, B, out);
-    {
-        const int64_t tot = nb * NODE_SZ;
-        hipLaunchKernelGGL(k_lift, dim3((tot + 255) / 256), dim3(256), 0, f->cur, params, f->prm + OFF_W0,
-                           f->prm + OFF_B0, f->V[0], tot);
-        TRY(launched());
-    }
+    hipLaunchKernelGGL(k_lift, dim3(B * N * N / LIFT_LINES), dim3(256), 0, f->cur, params, f->prm + OFF_W0,
+                       f->prm + OFF_B0, f->V[0]);
+    TRY(launched());
     const int64_t szN = nb * NODE_SZ, sz1 = nb * X1_SZ, sz3 = nb * X3_SZ;
     float* v = f->V[0];
     for (int l = 0; l < LAYERS; ++l) {
@@ -1850,14 +1997,12 @@ tf_status forward_body(tf_fno* f, const float* params, const float* hw, int B, f
         TRY(yexpand(f, f->gs, f->T2, f->T1, B));
         float* nv = f->training ? f->V[l + 1] : (v == f->V[0] ? f->V[1] : f->V[0]);
         LineArgs a{f->gx, f->T1, v, f->wb[l], f->prm + off_b(l), nullptr,
-                   (f->training && l < LAYERS - 1) ? f->Z[l] : nullptr, nv, B * N * N, 0, l < LAYERS - 1};
-        hipLaunchKernelGGL(k_lineout, dim3((B * N * N + 3) / 4), dim3(256), 0, f->cur, a);
-        TRY(launched());
+                   (f->training && l < LAYERS - 1) ? f->Z[l] : nullptr, nv, 0, l < LAYERS - 1};
+        TRY(lineout<false>(f, a, B));
         v = nv;
     }
-    ProjArgs p{v, f->p1b, f->prm + OFF_C1, f->p2e, f->c2e, out, nullptr, nullptr, nullptr, nullptr,
-               B * (N3 / 32), 0};
-    hipLaunchKernelGGL(k_proj, dim3((p.ntiles + 3) / 4), dim3(256), 0, f->cur, p);
+    const ProjArgs p{v, f->p1b, f->p1f, f->prm + OFF_C1, f->p2e, f->p2k, f->c2e, out, nullptr, nullptr, nullptr, nullptr};
+    hipLaunchKernelGGL(k_proj<false>, dim3(B * (N3 / 256)), dim3(256), 0, f->cur, p);
     return launched();
 }
 
@@ -1866,10 +2011,10 @@ tf_status forward_body(tf_fno* f, const float* params, const float* hw, int B, f
 tf_status forward_infer(tf_fno* f, const float* params, int B, float* out) {
     const int64_t nb = B;
     const int64_t sz3 = nb * X3_SZ;
-    const int lines = B * N * N;
+    const int lines = B * N * N, lpw = lines_per_wave(lines);
     InfArgs a{f->gx, f->fx, f->T1, nullptr, params, f->prm + OFF_W0, f->prm + OFF_B0, nullptr, nullptr,
-              nullptr, f->T1, f->p1k, f->prm + OFF_C1, f->p2k, f->c2e, out, lines};
-    hipLaunchKernelGGL(k_lift_x, dim3((lines + 3) / 4), dim3(256), 0, f->cur, a);
+              nullptr, f->T1, f->p1k, f->prm + OFF_C1, f->p2k, f->c2e, out, lpw};
+    hipLaunchKernelGGL(k_lift_x, dim3(lines / (4 * lpw)), dim3(256), 0, f->cur, a);
     TRY(launched());
     const float* v = nullptr;                 // v_0 is recomputed, never stored
     for (int l = 0; l < LAYERS; ++l) {
@@ -1884,10 +2029,11 @@ tf_status forward_infer(tf_fno* f, const float* params, int B, float* out) {
         if (l < LAYERS - 1) {
             float* nv = (v == f->V[0]) ? f->V[1] : f->V[0];
             a.vout = nv;
-            hipLaunchKernelGGL(k_line_fwd, dim3((lines + 3) / 4), dim3(256), 0, f->cur, a);
+            if (v) hipLaunchKernelGGL(k_line_fwd<false>, dim3(lines / (4 * lpw)), dim3(256), 0, f->cur, a);
+            else hipLaunchKernelGGL(k_line_fwd<true>, dim3(lines / (4 * lpw)), dim3(256), 0, f->cur, a);
             v = nv;
         } else {
-            hipLaunchKernelGGL(k_line_proj, dim3((2 * lines + 3) / 4), dim3(256), 0, f->cur, a);
+            hipLaunchKernelGGL(k_line_proj, dim3(lines / (2 * lpw)), dim3(256), 0, f->cur, a);
         }
         TRY(launched());
     }
@@ -1922,9 +2068,9 @@ tf_status backward(tf_fno* f, const float* params, const float* hw, const float*
     TRY(launched());
     // projection
     float* g = f->G[0];
-    ProjArgs p{f->V[3], f->p1b, f->prm + OFF_C1, f->p2e, f->c2e, nullptr, f->gout, g, f->hT, f->ghT,
-               B * (N3 / 32), 1};
-    hipLaunchKernelGGL(k_proj, dim3((p.ntiles + 3) / 4), dim3(256), 0, f->cur, p);
+    const ProjArgs p{f->V[3], f->p1b, f->p1f, f->prm + OFF_C1, f->p2e, f->p2k, f->c2e, nullptr, f->gout, g, f->hT,
+                     f->ghT};
+    hipLaunchKernelGGL(k_proj<true>, dim3(B * (N3 / 256)), dim3(256), 0, f->cur, p);
     TRY(launched());
     {   // [P1; c1] = [v3 | 1]^T dL/dpre
         GradArgs a{f->V[3], f->ghT, NODE_SZ * 4, int64_t(HID) * N3 * 2, f->part, C, HID};
@@ -1966,9 +2112,8 @@ tf_status backward(tf_fno* f, const float* params, const float* hw, const float*
         // adjoint of the forward transform, then the x line with the pointwise branch
         TRY(zexpand(f, f->fsT, f->Y2, f->T2, B));
         TRY(yexpand(f, f->fsT, f->T2, f->T1, B));
-        LineArgs a{f->fxT, f->T1, g, f->wb[l], nullptr, l > 0 ? f->Z[l - 1] : nullptr, nullptr, gn, B * N * N, 1, 0};
-        hipLaunchKernelGGL(k_lineout, dim3((B * N * N + 3) / 4), dim3(256), 0, f->cur, a);
-        TRY(launched());
+        LineArgs a{f->fxT, f->T1, g, f->wb[l], nullptr, l > 0 ? f->Z[l - 1] : nullptr, nullptr, gn, 0, 0};
+        TRY(lineout<true>(f, a, B));
         g = gn;
     }
     hipLaunchKernelGGL(k_lift_grad_part, dim3(N, B), dim3(256), 0, f->cur, g, f->part);
@@ -2254,9 +2399,8 @@ tf_status tf_fno_spectral_inverse(tf_fno* f, const float* modes, int32_t batch, 
     if (!modes || !u) return fail(TF_EINVAL, "NULL argument");
     TRY(zexpand(f, f->gs, modes, f->T2, batch));
     TRY(yexpand(f, f->gs, f->T2, f->T1, batch));
-    LineArgs a{f->gx, f->T1, nullptr, f->wb[0], nullptr, nullptr, nullptr, u, batch * N * N, 0, 0};
-    hipLaunchKernelGGL(k_lineout, dim3((batch * N * N + 3) / 4), dim3(256), 0, f->cur, a);
-    return launched();
+    LineArgs a{f->gx, f->T1, nullptr, f->wb[0], nullptr, nullptr, nullptr, u, 0, 0};
+    return lineout<false>(f, a, batch);
 }
 
 // Checkpoint: magic, version, parameter count, Adam step, then the fp32
