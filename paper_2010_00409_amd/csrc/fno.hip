@@ -465,8 +465,8 @@ struct GradArgs {
 // in steps of 16, the order of the products that of k_gemm; the row of ones
 // that gives the bias gradient is a constant A operand.  A wave's loads bound
 // it, there being one or two waves per SIMD at 16 samples: DEPTH steps are in
-// flight in registers.  16 samples: [W; b] 442 us through LDS -> LIN, [P1; c1]
-// 514 -> LP1, [P2; c2] 652 -> LP2.
+// flight in registers.  16 samples: [W; b] 442 us with the operands staged in
+// LDS (k_gemm), 200 so (5.4 TB/s); [P2; c2] 652 -> 195, [P1; c1] 514 -> 364.
 template <typename FA, typename FB>
 __global__ __launch_bounds__(64) void k_wgrad(GradArgs a) {
     constexpr int DEPTH = 8, TA = FA::TILES, TB = FB::TILES;
@@ -610,7 +610,8 @@ struct LineArgs {
 };
 
 // Memory bounds it (16 samples, z kept or read: 1.8 GB, 370 us at a copy's
-// rate): LO0 us with one line per wave and the matrices split by each, LO1 so.
+// rate): 429 us (mean of a step's six) with one line per wave and the matrices split
+// by each, 345 so.
 template <bool BWD>
 __global__ __launch_bounds__(256, 3) void k_lineout(LineArgs a) {
     __shared__ bf16x8 cm[2][2][2][64];
@@ -742,7 +743,7 @@ __device__ __forceinline__ void ld_kappa(const float* p, int s, int grp, float v
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 
-// 16 samples: forward PF0 -> PF1 us, backward PB0 -> PB1 us with one tile of
+// 16 samples: forward 558 -> 360 us, backward 1835 -> 890 us with one tile of
 // neighbouring nodes per wave and 2-byte stores before; the GELUs bound the
 // forward pass, the stores of the hidden layer (2.1 GB) the backward one.
 template <bool BWD>
@@ -900,8 +901,8 @@ __device__ __forceinline__ float lift_at(float base, const float* w0, int c, int
 }
 
 // One block per (z, y) pair of lines: a thread keeps four channels and walks two
-// lines of nodes in 16-byte stores.  16 samples: LI0 us with one element per
-// thread, each summing its base anew, LI1 so (537 MB).
+// lines of nodes in 16-byte stores.  16 samples: 330 us with one element per
+// thread, each summing its base anew, 88 so (537 MB).
 constexpr int LIFT_LINES = 8;             // lines per block (64 divides into them)
 __global__ __launch_bounds__(256) void k_lift(const float* p, const float* w0, const float* b0, float* v) {
     const int line0 = blockIdx.x * LIFT_LINES, b = line0 / (N * N), z = line0 / N % N;
@@ -966,7 +967,7 @@ struct InfArgs {
 
 // Lift and the first x contraction, one wave per x-line:
 //   X1[(s,kx)][c] = sum_x Fx[(s,kx)][x] v0[x][c]    (split bf16)
-// Batch 64: LX0 us with the matrix split by every wave, LX1 so (805 MB written,
+// Batch 64: 305 us with the matrix split by every wave, 149 so (805 MB written,
 // 165 us at a copy's rate).  The y and z terms of the lift are fused into the
 // sum for x < 16 and rounded first beyond: the windows of a trained surrogate
 // stay the same bits that this operator has always given (a float32 rounding
@@ -1015,8 +1016,8 @@ __global__ __launch_bounds__(256) void k_lift_x(InfArgs a) {
 // of lane (o, g), so it is the B operand of the contraction over x with the
 // constant Fx gathered in that order.  LIFT: v_l is v_0, recomputed from the
 // parameters, never stored.  Memory bounds it (batch 64: 3.8 GB and, with v_l
-// read, 5.9): LF0 us, LF0b with one line per wave and the matrices split by
-// each, LF1 and LF1b so.
+// read, 5.9): 1.32 ms and 1.50 with one line per wave and the matrices
+// split by each, 0.77 and 1.21 so.
 template <bool LIFT>
 __global__ __launch_bounds__(256, 3) void k_line_fwd(InfArgs a) {
     __shared__ bf16x8 gx[2][2][2][64], fx[4][2][64];
@@ -1120,7 +1121,7 @@ __global__ __launch_bounds__(256, 3) void k_line_fwd(InfArgs a) {
 // projection then runs as in k_proj.  A wave takes one half (32 nodes) of its
 // lines: twice the independent waves.  The constant operands are in LDS; the
 // 64 GELUs per lane and half line bound it (batch 64: 2.1e9 of about 22
-// instructions, 1.2 ms): LP0 us with the operands loaded by every wave, LP1 so.
+// instructions, 1.2 ms): 1.82 ms with the operands loaded by every wave, 1.65 so.
 __global__ __launch_bounds__(256, 4) void k_line_proj(InfArgs a) {
     __shared__ bf16x8 gx[2][2][2][64], p1s[8][64], p2s[8][64];
     __shared__ __attribute__((aligned(16))) float c1s[HID], bs[C];
@@ -1214,7 +1215,7 @@ __global__ __launch_bounds__(256, 4) void k_line_proj(InfArgs a) {
 
 // per (sample, z plane): sum_node g, and sum_node coord_d g, for every channel;
 // thread (ng, c) takes the nodes ng (mod 8) in increasing order, sixteen loads
-// in flight (16 samples: LG0 us with one, LG1 so; 537 MB)
+// in flight (16 samples: 253 us with one, 118 so; 537 MB)
 __global__ __launch_bounds__(256) void k_lift_grad_part(const float* gv, float* part) {
     const int z = blockIdx.x, b = blockIdx.y;
     const int c = threadIdx.x & 31, ng = threadIdx.x >> 5;
