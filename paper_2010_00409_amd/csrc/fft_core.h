@@ -168,8 +168,9 @@ template <typename T, int P, int Q, int DIR> __device__ __forceinline__ void dft
 }
 
 template <typename T, int R, int DIR> __device__ __forceinline__ void dftR(C2<T>* v) {
-    static_assert(R == 2 || R == 3 || R == 4 || R == 5 || R == 7 || R == 8 || R == 20 || R == 24 || R == 28,
-                  "radix 2, 3, 4, 5, 7, 8, 20, 24 or 28");
+    static_assert(R == 1 || R == 2 || R == 3 || R == 4 || R == 5 || R == 7 || R == 8 || R == 20 || R == 24 || R == 28,
+                  "radix 1, 2, 3, 4, 5, 7, 8, 20, 24 or 28");
+    if constexpr (R == 1) return;
     if constexpr (R == 20) { dft_coprime<T, 5, 4, DIR>(v); return; }
     if constexpr (R == 24) { dft_coprime<T, 3, 8, DIR>(v); return; }
     if constexpr (R == 28) { dft_coprime<T, 7, 4, DIR>(v); return; }
