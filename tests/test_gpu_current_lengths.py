@@ -25,7 +25,7 @@ def inputs(shape):
 
 
 @pytest.mark.parametrize("prec", ["f64", "f32"])
-@pytest.mark.parametrize("nz", [8, 16, 24, 40, 56, 64, 80, 112, 128, 192, 224, 320, 384, 448, 512, 640, 768, 1024])
+@pytest.mark.parametrize("nz", [8, 16, 24, 40, 56, 64, 80, 112, 128, 192, 224, 256, 320, 384, 448, 512, 640, 768, 1024])
 def test_current_step_over_z_lengths(nz, prec):
     import torch
     if prec == "f64" and nz > 768:
