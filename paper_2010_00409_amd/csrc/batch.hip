@@ -367,7 +367,7 @@ tf_status tf_batch_create(const tf_grid* grids, const tf_pulse* pulses, int32_t 
         return fail(TF_ENOMEM, "batch needs " + std::to_string(need) + " device bytes, above TFOCUS_MAX_DEVICE_BYTES");
     }
     auto alloc = [&](void** p, size_t bytes, size_t* got = nullptr) -> tf_status {
-        hipError_t e = got ? BlockCache::get().take(p, bytes, got) : hipMalloc(p, bytes);
+        hipError_t e = got ? BlockCache::get().take(p, bytes, got) : BlockCache::get().alloc(p, bytes);
         if (e == hipErrorOutOfMemory) return fail(TF_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
         if (e != hipSuccess) return fail(TF_EDEVICE, std::string("hipMalloc: ") + hipGetErrorString(e));
         return TF_OK;
@@ -570,8 +570,8 @@ tf_status tf_tune(const int32_t* sizes, int32_t n, int32_t precision, const char
         g.dx = g.dy = g.dz = 1.0;
         const size_t cells = (size_t)N * N * N;
         TuneBuffers tb;
-        TF_HIP(hipMalloc(&tb.state, 6 * cells * es));
-        TF_HIP(hipMalloc(&tb.spec, 6 * cells * es));
+        TF_HIP(tf::host::BlockCache::get().alloc(&tb.state, 6 * cells * es));
+        TF_HIP(tf::host::BlockCache::get().alloc(&tb.spec, 6 * cells * es));
         for (int a = 0; a < 3; ++a) {
             TF_HIP(hipMalloc(&tb.tw[a], 2 * es * N));
             TF_HIP(upload_twiddles(tb.tw[a], N, precision, nullptr));

@@ -48,10 +48,11 @@ inline bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 // batch (19 GB) cost some 15 times its kernels.  A block enters after the
 // device has been synchronised (what hipFree would do), so no queued work
 // of any stream still uses it.  Bounds: blocks of 32 MB and more, an eighth
-// of the device's memory in all; a block that four later requests pass over
-// is given back, all are when an allocation fails, and when a surrogate is
-// created (the next consumer of the windows a batch made).  One mutex: any
-// thread may create and destroy objects.
+// of the device's memory in all, and none while less than half of it is free
+// (others' allocations come first); a block that four later requests pass over
+// is given back, all are when an allocation of the library fails, and when a
+// surrogate is created (the next consumer of the windows a batch made).  One
+// mutex: any thread may create and destroy objects.
 class BlockCache {
 public:
     static BlockCache& get();
@@ -61,6 +62,9 @@ public:
     void put(void* ptr, size_t bytes);
     // Give every kept block back.
     void clear();
+    // hipMalloc, with every kept block given back before it reports that the
+    // memory is out.
+    hipError_t alloc(void** ptr, size_t bytes);
 
 private:
     struct Block { int dev; void* ptr; size_t bytes; int passed; };

@@ -1685,7 +1685,7 @@ struct tf_fno {
     template <typename T>
     tf_status alloc(T** p, int64_t n) {
         void* q = nullptr;
-        const hipError_t e = hipMalloc(&q, size_t(n) * sizeof(T));
+        const hipError_t e = tf::host::BlockCache::get().alloc(&q, size_t(n) * sizeof(T));
         if (e != hipSuccess) return fail(TF_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
         allocs.push_back(q);
         *p = (T*)q;
@@ -2143,7 +2143,7 @@ struct CallBuffers {
     template <typename T>
     tf_status alloc(T** p, int64_t n) {
         void* q = nullptr;
-        const hipError_t e = hipMalloc(&q, size_t(n) * sizeof(T));
+        const hipError_t e = tf::host::BlockCache::get().alloc(&q, size_t(n) * sizeof(T));
         if (e != hipSuccess) return fail(TF_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
         ptrs.push_back(q);
         *p = static_cast<T*>(q);

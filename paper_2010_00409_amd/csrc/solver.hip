@@ -44,9 +44,19 @@ void BlockCache::clear() {
     clear_locked();
 }
 
+hipError_t BlockCache::alloc(void** ptr, size_t bytes) {
+    hipError_t e = hipMalloc(ptr, bytes);
+    if (e != hipErrorOutOfMemory) return e;
+    std::lock_guard<std::mutex> lk(mu_);
+    if (free_.empty()) return e;
+    (void)hipGetLastError();
+    clear_locked();
+    return hipMalloc(ptr, bytes);
+}
+
 hipError_t BlockCache::take(void** ptr, size_t bytes, size_t* got) {
     *got = bytes;
-    if (bytes < CACHE_MIN_BLOCK) return hipMalloc(ptr, bytes);
+    if (bytes < CACHE_MIN_BLOCK) return alloc(ptr, bytes);
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -85,7 +95,7 @@ void BlockCache::put(void* ptr, size_t bytes) {
     int dev = 0;
     size_t avail = 0, total = 0;
     if (bytes < CACHE_MIN_BLOCK || hipGetDevice(&dev) != hipSuccess || hipDeviceSynchronize() != hipSuccess ||
-        hipMemGetInfo(&avail, &total) != hipSuccess || bytes > total / 8) {
+        hipMemGetInfo(&avail, &total) != hipSuccess || bytes > total / 8 || avail < total / 2) {
         (void)hipFree(ptr);
         return;
     }
@@ -528,7 +538,7 @@ tf_status tf_create(const tf_grid* grid, int32_t precision, void* hip_stream, tf
         return fail(TF_ENOMEM, "solver needs " + std::to_string(need) + " device bytes, above TFOCUS_MAX_DEVICE_BYTES");
     }
     auto alloc = [&](void** p, size_t b, size_t* got = nullptr) -> tf_status {
-        hipError_t e = got ? BlockCache::get().take(p, b, got) : hipMalloc(p, b);
+        hipError_t e = got ? BlockCache::get().take(p, b, got) : BlockCache::get().alloc(p, b);
         if (e == hipErrorOutOfMemory) return fail(TF_ENOMEM, "hipMalloc of " + std::to_string(b) + " bytes failed");
         if (e != hipSuccess) return fail(TF_EDEVICE, std::string("hipMalloc: ") + hipGetErrorString(e));
         return TF_OK;
@@ -622,7 +632,7 @@ tf_status tf_set_pulse(tf_solver* s, const tf_pulse* pulse, tf_pulse_info* info)
             if (s->pulse_host) (void)hipHostFree(s->pulse_host);
             s->pulse_tab = s->pulse_host = nullptr;
             s->pulse_tab_len = s->pulse_host_len = 0;
-            TF_HIP(hipMalloc(&s->pulse_tab, len * sizeof(double)));
+            TF_HIP(BlockCache::get().alloc(reinterpret_cast<void**>(&s->pulse_tab), len * sizeof(double)));
             s->pulse_tab_len = len;
             TF_HIP(hipHostMalloc(&s->pulse_host, all.size() * sizeof(double)));
             s->pulse_host_len = all.size();
@@ -695,7 +705,7 @@ tf_status tf_advance_current(tf_solver* s, const void* j, int32_t j_on_device, d
             return fail(TF_ENOMEM, "current steps need " + std::to_string(bytes6 + spec_b) +
                                        " more device bytes, above TFOCUS_MAX_DEVICE_BYTES");
         auto alloc = [&](void** p, size_t bytes, const char* what) -> tf_status {
-            hipError_t e = hipMalloc(p, bytes);
+            hipError_t e = BlockCache::get().alloc(p, bytes);
             if (e == hipSuccess) return TF_OK;
             *p = nullptr;
             return fail(e == hipErrorOutOfMemory ? TF_ENOMEM : TF_EDEVICE, std::string(what) + hipGetErrorString(e));
@@ -746,7 +756,7 @@ tf_status tf_read_focal(tf_solver* s, const tf_window* w, void* dst, int32_t dst
                 s->scratch_out = nullptr;
                 s->scratch_bytes = 0;
             }
-            TF_HIP(hipMalloc(&s->scratch_out, bytes));
+            TF_HIP(BlockCache::get().alloc(&s->scratch_out, bytes));
             s->scratch_bytes = bytes;
         }
         out = s->scratch_out;
