@@ -47,7 +47,10 @@ def pass_kernels(plan, nz):
         z, col = "k_z", "k_col"
     else:
         waves = {512: "k_z_wave", 256: "k_z_wave256"}
-        z, col = (waves[nz] if zv >= 7 and nz in waves else "k_z_fast"), "k_col_fast"
+        z = waves[nz] if zv >= 7 and nz in waves else "k_z_fast" if nz in (128, 192, 256, 512) else "k_z_res"
+        col = "k_col_fast"
+    # x_inverse: all but the last launch of a run are k_x_pair, which goes on to
+    # the next step's forward transform
     return {"x_forward": "k_x_forward", "y_forward": col, "z_step": z, "y_inverse": col,
             "x_inverse": "k_x_inverse"}
 
@@ -447,7 +450,11 @@ def main():
     kernels = pass_kernels(tf.tf_kernel_plan(grid, prec), n[2])
     traffic = traffic_record(kernels[dom])
     step_ms = sum(passes[k][0] for k in step_passes) / (steps * args.steps)
-    hbm_gbs = PASS_BYTES_PER_CELL[prec] * len(step_passes) * cells / (step_ms / 1e3) / 1e9
+    # within a run the inverse x pass of a step and the forward one of the next
+    # are one launch (recorded as x_inverse), which reads and writes the spectrum
+    # once: a step is four passes of these bytes, the last of a run five
+    launches = sum(passes[k][1] for k in step_passes)
+    hbm_gbs = alg_bytes * launches / (step_ms * steps * args.steps / 1e3) / 1e9
 
     line = {
         "metric": METRIC,

@@ -47,8 +47,8 @@ def _gemm_args(name):
 def _short(name):
     if "k_gemm" in name:                      # surrogate GEMM: keep the tile shape and types
         return "k_gemm<" + _gemm_args(name) + ">"
-    for key in ("k_z_fast", "k_z_wave", "k_col_fast", "k_x_forward", "k_x_inverse", "k_init_map", "k_readout",
-                "k_lift_x", "k_line_fwd", "k_line_proj", "k_lineout", "k_proj", "k_head_eff",
+    for key in ("k_z_fast", "k_z_wave", "k_z_res", "k_col_fast", "k_x_forward", "k_x_inverse", "k_x_pair", "k_init_map",
+                "k_readout", "k_axis", "k_wgrad", "k_lift_x", "k_line_fwd", "k_line_proj", "k_lineout", "k_proj", "k_head_eff",
                 "k_col", "k_z", "k_sumsq", "k_reduce", "copy"):
         if key in name:
             return key
