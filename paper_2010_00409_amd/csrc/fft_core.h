@@ -295,10 +295,12 @@ template <int N, int E> struct LGPlan {
 // S2 = 1 adds one pad slot every 32 elements, S2 = 8 one every 8 elements
 // (contiguous regions; the finer pad spreads the 8-element runs of the
 // radix-8 Stockham writes over distinct banks), S2 = 0 none; S > 1
-// interleaves the regions of neighbouring groups (column tiles).
+// interleaves the regions of neighbouring groups (column tiles), where S2 =
+// lg_pad(PSH, PAD) adds PAD slots every 2^PSH elements.
+constexpr int lg_pad(int psh, int pad) { return 16 * pad + psh; }
 template <int N, int S, int S2> struct LgAt {
-    static constexpr int PSH = S2 == 8 ? 3 : 5;
-    static constexpr int PAD = S2 == 8 ? 1 : S2;
+    static constexpr int PSH = S2 >= 16 ? S2 % 16 : S2 == 8 ? 3 : 5;
+    static constexpr int PAD = S2 >= 16 ? S2 / 16 : S2 == 8 ? 1 : S2;
     __device__ __forceinline__ static int at(int n) { return n * S + (n >> PSH) * PAD; }
     static constexpr int span = (N - 1) * S + ((N - 1) >> PSH) * PAD + 1;
 };
