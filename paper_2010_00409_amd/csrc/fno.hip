@@ -96,9 +96,6 @@ __device__ __forceinline__ float gelu_d(float x) {
     return 0.5f * (1.0f + erf_as(x * 0.70710678118654752f)) + x * ex * 0.39894228040143268f;
 }
 
-__device__ __forceinline__ float ldf(const float* p) { return *p; }
-__device__ __forceinline__ float ldf(const bf16* p) { return (float)*p; }
-
 // ---------------------------------------------------------------------------
 // Generic strided GEMM  C[b] = A[b] (M x K) . B[b] (K x N)
 // ---------------------------------------------------------------------------
