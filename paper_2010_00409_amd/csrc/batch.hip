@@ -146,9 +146,9 @@ struct Group {
     std::vector<int> slot_of;        // slot -> instance id (for the current run)
     long cells = 0;
     size_t state_elems = 0, spec_elems = 0;   // per slot
-    void* state = nullptr;           // state and spec: blocks of the cache, with their sizes
+    void* state = nullptr;           // in state_block
     void* spec = nullptr;
-    size_t state_bytes = 0, spec_bytes = 0;
+    DeviceBlock state_block, spec_block;
     void* tw[3] = {nullptr, nullptr, nullptr};
     double* cdt = nullptr;           // per slot
     tf::RowMap rm{};
@@ -186,8 +186,8 @@ namespace {
 void batch_free(tf_batch* b) {
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     for (Group& g : b->groups) {
-        BlockCache::get().put(g.state, g.state_bytes);
-        BlockCache::get().put(g.spec, g.spec_bytes);
+        BlockCache::get().put(g.state_block);
+        BlockCache::get().put(g.spec_block);
         void* ps[] = {g.tw[0], g.tw[1], g.tw[2], g.cdt};
         for (void* p : ps)
             if (p) (void)hipFree(p);
@@ -366,12 +366,13 @@ tf_status tf_batch_create(const tf_grid* grids, const tf_pulse* pulses, int32_t 
         delete b;
         return fail(TF_ENOMEM, "batch needs " + std::to_string(need) + " device bytes, above TFOCUS_MAX_DEVICE_BYTES");
     }
-    auto alloc = [&](void** p, size_t bytes, size_t* got = nullptr) -> tf_status {
-        hipError_t e = got ? BlockCache::get().take(p, bytes, got) : BlockCache::get().alloc(p, bytes);
+    auto made = [](hipError_t e, size_t bytes) -> tf_status {
         if (e == hipErrorOutOfMemory) return fail(TF_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
         if (e != hipSuccess) return fail(TF_EDEVICE, std::string("hipMalloc: ") + hipGetErrorString(e));
         return TF_OK;
     };
+    auto alloc = [&](void** p, size_t bytes) { return made(BlockCache::get().alloc(p, bytes), bytes); };
+    auto take = [&](DeviceBlock* block, size_t bytes) { return made(BlockCache::get().take(block, bytes), bytes); };
     tf_status st = TF_OK;
     for (Group& G : b->groups) {
         if (st != TF_OK) break;
@@ -382,8 +383,10 @@ tf_status tf_batch_create(const tf_grid* grids, const tf_pulse* pulses, int32_t 
         G.kp = plan_for(g, precision);
         G.rm = tf::RowMap(g.ny, g.nz, G.kp.row_block);
         const size_t m = G.members.size();
-        st = alloc(&G.state, m * G.state_elems * b->esize, &G.state_bytes);
-        if (st == TF_OK) st = alloc(&G.spec, m * G.spec_elems * b->esize, &G.spec_bytes);
+        st = take(&G.state_block, m * G.state_elems * b->esize);
+        if (st == TF_OK) st = take(&G.spec_block, m * G.spec_elems * b->esize);
+        G.state = G.state_block.ptr;
+        G.spec = G.spec_block.ptr;
         const int ns[3] = {g.nx, g.ny, g.nz};
         for (int a = 0; a < 3 && st == TF_OK; ++a) st = alloc(&G.tw[a], 2 * b->esize * ns[a]);
         if (st == TF_OK) st = alloc((void**)&G.cdt, m * sizeof(double));

@@ -9,11 +9,11 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
-#include <mutex>
 #include <string>
 #include <vector>
 
 #include "../../include/tfocus.h"
+#include "block_cache.h"
 #include "kernels.h"
 
 namespace tf {
@@ -39,39 +39,6 @@ inline bool length_ok(int n) {
 }
 
 inline bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
-
-// ---- device blocks kept from one solver or batch for the next ----
-
-// Large device allocations of destroyed solvers and batches, kept for the
-// next one of about the same size: a freed block's pages are wiped and
-// mapped anew at about 35 GB/s, which made the allocation of a 64-window
-// batch (19 GB) cost some 15 times its kernels.  A block enters after the
-// device has been synchronised (what hipFree would do), so no queued work
-// of any stream still uses it.  Bounds: blocks of 32 MB and more, an eighth
-// of the device's memory in all, and none while less than half of it is free
-// (others' allocations come first); a block that four later requests pass over
-// is given back, all are when an allocation of the library fails, and when a
-// surrogate is created (the next consumer of the windows a batch made).  One
-// mutex: any thread may create and destroy objects.
-class BlockCache {
-public:
-    static BlockCache& get();
-    // A block of at least `bytes` on the current device; *got its size.
-    hipError_t take(void** ptr, size_t bytes, size_t* got);
-    // Back into the cache (or to the device, where it does not fit the bounds).
-    void put(void* ptr, size_t bytes);
-    // Give every kept block back.
-    void clear();
-    // hipMalloc, with every kept block given back before it reports that the
-    // memory is out.
-    hipError_t alloc(void** ptr, size_t bytes);
-
-private:
-    struct Block { int dev; void* ptr; size_t bytes; int passed; };
-    std::mutex mu_;
-    std::vector<Block> free_;
-    void clear_locked();
-};
 
 // ---- pulse geometry (host, float64) ----
 

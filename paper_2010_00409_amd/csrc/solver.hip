@@ -24,95 +24,6 @@ std::string& tf::host::last_error() {
     return e;
 }
 
-namespace tf {
-namespace host {
-
-BlockCache& BlockCache::get() {
-    static BlockCache* c = new BlockCache();      // lives until the process ends
-    return *c;
-}
-
-constexpr size_t CACHE_MIN_BLOCK = size_t(32) << 20;
-
-void BlockCache::clear_locked() {
-    for (const Block& b : free_) (void)hipFree(b.ptr);
-    free_.clear();
-}
-
-void BlockCache::clear() {
-    std::lock_guard<std::mutex> lk(mu_);
-    clear_locked();
-}
-
-hipError_t BlockCache::alloc(void** ptr, size_t bytes) {
-    hipError_t e = hipMalloc(ptr, bytes);
-    if (e != hipErrorOutOfMemory) return e;
-    std::lock_guard<std::mutex> lk(mu_);
-    if (free_.empty()) return e;
-    (void)hipGetLastError();
-    clear_locked();
-    return hipMalloc(ptr, bytes);
-}
-
-hipError_t BlockCache::take(void** ptr, size_t bytes, size_t* got) {
-    *got = bytes;
-    if (bytes < CACHE_MIN_BLOCK) return alloc(ptr, bytes);
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    std::lock_guard<std::mutex> lk(mu_);
-    // the smallest block that holds the request with at most a quarter to spare
-    size_t best = free_.size();
-    for (size_t i = 0; i < free_.size(); ++i)
-        if (free_[i].dev == dev && free_[i].bytes >= bytes && free_[i].bytes <= bytes + bytes / 4 &&
-            (best == free_.size() || free_[i].bytes < free_[best].bytes))
-            best = i;
-    if (best < free_.size()) {
-        *ptr = free_[best].ptr;
-        *got = free_[best].bytes;
-        free_.erase(free_.begin() + (long)best);
-        return hipSuccess;
-    }
-    for (size_t i = 0; i < free_.size();) {
-        if (++free_[i].passed > 4) {
-            (void)hipFree(free_[i].ptr);
-            free_.erase(free_.begin() + (long)i);
-        } else {
-            ++i;
-        }
-    }
-    e = hipMalloc(ptr, bytes);
-    if (e == hipErrorOutOfMemory && !free_.empty()) {
-        (void)hipGetLastError();
-        clear_locked();
-        e = hipMalloc(ptr, bytes);
-    }
-    return e;
-}
-
-void BlockCache::put(void* ptr, size_t bytes) {
-    if (!ptr) return;
-    int dev = 0;
-    size_t avail = 0, total = 0;
-    if (bytes < CACHE_MIN_BLOCK || hipGetDevice(&dev) != hipSuccess || hipDeviceSynchronize() != hipSuccess ||
-        hipMemGetInfo(&avail, &total) != hipSuccess || bytes > total / 8 || avail < total / 2) {
-        (void)hipFree(ptr);
-        return;
-    }
-    std::lock_guard<std::mutex> lk(mu_);
-    size_t held = bytes;
-    for (const Block& b : free_) held += b.bytes;
-    while (held > total / 8 && !free_.empty()) {          // the oldest first
-        held -= free_.front().bytes;
-        (void)hipFree(free_.front().ptr);
-        free_.erase(free_.begin());
-    }
-    free_.push_back({dev, ptr, bytes, 0});
-}
-
-}  // namespace host
-}  // namespace tf
-
 struct tf_solver {
     tf_grid grid{};
     int prec = TF_F32;
@@ -120,9 +31,9 @@ struct tf_solver {
     hipStream_t stream = nullptr;
     long cells = 0;
     int nkx = 0;
-    void* state = nullptr;         // state and spec: blocks of the cache, with their sizes
+    void* state = nullptr;         // in state_block
     void* spec = nullptr;
-    size_t state_bytes = 0, spec_bytes = 0;
+    DeviceBlock state_block, spec_block;
     void* tw[3] = {nullptr, nullptr, nullptr};
     double* partials = nullptr;
     size_t npartials = 0;
@@ -350,8 +261,8 @@ void free_all(tf_solver* s) {
     s->pulse_host = nullptr;
     for (hipEvent_t ev : s->evpool) (void)hipEventDestroy(ev);
     s->evpool.clear();
-    BlockCache::get().put(s->state, s->state_bytes);
-    BlockCache::get().put(s->spec, s->spec_bytes);
+    BlockCache::get().put(s->state_block);
+    BlockCache::get().put(s->spec_block);
     s->state = s->spec = nullptr;
     void* ptrs[] = {s->tw[0], s->tw[1], s->tw[2], s->partials, s->results,
                     s->pulse_tab, s->dcbuf, s->scratch_out, s->jstate, s->jspec};
@@ -537,15 +448,16 @@ tf_status tf_create(const tf_grid* grid, int32_t precision, void* hip_stream, tf
         delete s;
         return fail(TF_ENOMEM, "solver needs " + std::to_string(need) + " device bytes, above TFOCUS_MAX_DEVICE_BYTES");
     }
-    auto alloc = [&](void** p, size_t b, size_t* got = nullptr) -> tf_status {
-        hipError_t e = got ? BlockCache::get().take(p, b, got) : BlockCache::get().alloc(p, b);
+    auto made = [](hipError_t e, size_t b) -> tf_status {
         if (e == hipErrorOutOfMemory) return fail(TF_ENOMEM, "hipMalloc of " + std::to_string(b) + " bytes failed");
         if (e != hipSuccess) return fail(TF_EDEVICE, std::string("hipMalloc: ") + hipGetErrorString(e));
         return TF_OK;
     };
-    tf_status st = TF_OK;
-    if (st == TF_OK) st = alloc(&s->state, state_b, &s->state_bytes);
-    if (st == TF_OK) st = alloc(&s->spec, spec_b, &s->spec_bytes);
+    auto alloc = [&](void** p, size_t b) { return made(BlockCache::get().alloc(p, b), b); };
+    tf_status st = made(BlockCache::get().take(&s->state_block, state_b), state_b);
+    if (st == TF_OK) st = made(BlockCache::get().take(&s->spec_block, spec_b), spec_b);
+    s->state = s->state_block.ptr;
+    s->spec = s->spec_block.ptr;
     const int ns[3] = {grid->nx, grid->ny, grid->nz};
     for (int a = 0; a < 3 && st == TF_OK; ++a) st = alloc(&s->tw[a], 2 * s->esize * ns[a]);
     if (st == TF_OK) st = alloc((void**)&s->partials, s->npartials * sizeof(double));
