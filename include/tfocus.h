@@ -177,8 +177,20 @@ tf_status tf_layer_grid(const tf_pulse* pulse, int32_t nx, int32_t ny, int32_t n
 tf_status tf_create(const tf_grid* grid, int32_t precision, void* hip_stream,
                     tf_solver** out);
 
-/* Free everything the solver owns (waits for its stream). NULL is a no-op. */
+/* Free everything the solver owns (waits for its stream). NULL is a no-op.
+ * Its two large device blocks (state and spectrum, from 32 MB on) are kept for
+ * the next tf_create or tf_batch_create of about that size, which may get up to
+ * a quarter more than it asks for: at most an eighth of the device's memory in
+ * all, none while less than half of it is free, none with
+ * TFOCUS_MAX_DEVICE_BYTES set.  They go back to the device when an allocation
+ * of the library fails, when later objects have no use for them, and by
+ * tf_release_memory. */
 tf_status tf_destroy(tf_solver* s);
+
+/* Give the device blocks kept from destroyed solvers and batches back to their
+ * devices, for allocators outside the library.  Any thread, any current
+ * device; objects in use are not touched. */
+tf_status tf_release_memory(void);
 
 /* Copy a state [6][nz][ny][nx] in, set the time to t.  The state is taken as
  * is (no projection).  Host sources are copied synchronously. */
@@ -340,6 +352,7 @@ tf_status tf_batch_run(tf_batch* b, const int64_t* nsteps, const double* dt, con
 /* Final state [6][nz][ny][nx] of instance i after the last run. */
 tf_status tf_batch_get_fields(tf_batch* b, int32_t i, void* dst, int32_t dst_on_device);
 
+/* Blocks are kept as by tf_destroy. */
 tf_status tf_batch_destroy(tf_batch* b);
 
 /* ---- kernel plans and the autotuner ------------------------------------ */

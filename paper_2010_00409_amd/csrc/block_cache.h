@@ -24,10 +24,13 @@ struct DeviceBlock {
 // enters after that device has been synchronised (what hipFree would do), so no
 // queued work of any stream still uses it.  Bounds: blocks of 32 MB and more, an
 // eighth of a device's memory, and none while less than half of that is free
-// (others' allocations come first); a block that four later requests on its
+// (others' allocations come first; looked at whenever a block comes in and
+// whenever a request finds none); a block that four later requests on its
 // device pass over is given back by the next one, all are when an allocation of
-// the library fails, and when a surrogate is created (the next consumer of the
-// windows a batch made).  One mutex: any thread may create and destroy objects.
+// the library fails, when a surrogate is created (the next consumer of the
+// windows a batch made) and by tf_release_memory.  With TFOCUS_MAX_DEVICE_BYTES
+// set, objects get exactly the bytes that the limit counts: nothing is kept or
+// handed out.  One mutex: any thread may create and destroy objects.
 class BlockCache {
 public:
     static BlockCache& get();
@@ -50,6 +53,7 @@ private:
     std::mutex mu_;
     std::vector<Kept> free_;
     void clear_locked();
+    void drop(int dev);          // every kept block of a device
     void put_current(const DeviceBlock& block);
 };
 

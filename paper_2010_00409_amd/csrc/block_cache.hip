@@ -1,5 +1,7 @@
 #include "block_cache.h"
 
+#include <cstdlib>
+
 namespace tf {
 namespace host {
 
@@ -10,9 +12,22 @@ BlockCache& BlockCache::get() {
 
 constexpr size_t CACHE_MIN_BLOCK = size_t(32) << 20;
 
+static bool limited() { return std::getenv("TFOCUS_MAX_DEVICE_BYTES") != nullptr; }
+
 void BlockCache::clear_locked() {
     for (const Kept& k : free_) (void)hipFree(k.block.ptr);
     free_.clear();
+}
+
+void BlockCache::drop(int dev) {
+    for (size_t i = 0; i < free_.size();) {
+        if (free_[i].block.dev == dev) {
+            (void)hipFree(free_[i].block.ptr);
+            free_.erase(free_.begin() + (long)i);
+        } else {
+            ++i;
+        }
+    }
 }
 
 void BlockCache::clear() {
@@ -34,7 +49,7 @@ hipError_t BlockCache::take(DeviceBlock* block, size_t bytes) {
     *block = DeviceBlock{nullptr, bytes, 0};
     hipError_t e = hipGetDevice(&block->dev);
     if (e != hipSuccess) return e;
-    if (bytes < CACHE_MIN_BLOCK) return alloc(&block->ptr, bytes);
+    if (bytes < CACHE_MIN_BLOCK || limited()) return alloc(&block->ptr, bytes);
     std::lock_guard<std::mutex> lk(mu_);
     // the smallest block that holds the request with at most a quarter to spare
     size_t best = free_.size();
@@ -57,6 +72,8 @@ hipError_t BlockCache::take(DeviceBlock* block, size_t bytes) {
             ++i;
         }
     }
+    size_t avail = 0, total = 0;
+    if (!free_.empty() && (hipMemGetInfo(&avail, &total) != hipSuccess || avail < total / 2)) drop(block->dev);
     e = hipMalloc(&block->ptr, bytes);
     if (e == hipErrorOutOfMemory && !free_.empty()) {
         (void)hipGetLastError();
@@ -80,12 +97,17 @@ void BlockCache::put(const DeviceBlock& block) {
 // put() with the block's device current.
 void BlockCache::put_current(const DeviceBlock& block) {
     size_t avail = 0, total = 0;
-    if (block.bytes < CACHE_MIN_BLOCK || hipDeviceSynchronize() != hipSuccess ||
-        hipMemGetInfo(&avail, &total) != hipSuccess || block.bytes > total / 8 || avail < total / 2) {
+    if (block.bytes < CACHE_MIN_BLOCK || limited() || hipDeviceSynchronize() != hipSuccess ||
+        hipMemGetInfo(&avail, &total) != hipSuccess || block.bytes > total / 8) {
         (void)hipFree(block.ptr);
         return;
     }
     std::lock_guard<std::mutex> lk(mu_);
+    if (avail < total / 2) {
+        (void)hipFree(block.ptr);
+        drop(block.dev);
+        return;
+    }
     size_t held = block.bytes;
     for (const Kept& k : free_) held += k.block.dev == block.dev ? k.block.bytes : 0;
     for (size_t i = 0; held > total / 8 && i < free_.size();) {          // the oldest first

@@ -490,6 +490,11 @@ tf_status tf_destroy(tf_solver* s) {
     return TF_OK;
 }
 
+tf_status tf_release_memory(void) {
+    BlockCache::get().clear();
+    return TF_OK;
+}
+
 tf_status tf_set_fields(tf_solver* s, const void* src, int32_t src_on_device, double t) {
     if (!s || !src) return fail(TF_EINVAL, "solver and src must not be NULL");
     if (!std::isfinite(t)) return fail(TF_EINVAL, "t must be finite");

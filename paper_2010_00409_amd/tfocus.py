@@ -81,6 +81,7 @@ _SIGS = {
                       ctypes.c_int),
     "tf_create": ([ctypes.POINTER(tf_grid), ctypes.c_int32, _P, ctypes.POINTER(_P)], ctypes.c_int),
     "tf_destroy": ([_P], ctypes.c_int),
+    "tf_release_memory": ([], ctypes.c_int),
     "tf_set_fields": ([_P, _P, ctypes.c_int32, ctypes.c_double], ctypes.c_int),
     "tf_get_fields": ([_P, _P, ctypes.c_int32], ctypes.c_int),
     "tf_state_ptr": ([_P, ctypes.POINTER(_P)], ctypes.c_int),
@@ -273,6 +274,11 @@ def tf_create(grid, precision="f32", stream=None):
 
 def tf_destroy(h):
     _check(load().tf_destroy(h))
+
+
+def tf_release_memory():
+    """Give the device blocks kept from destroyed solvers and batches back."""
+    _check(load().tf_release_memory())
 
 
 def tf_set_fields(h, src, t=0.0):

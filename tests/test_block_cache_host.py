@@ -148,3 +148,39 @@ def test_an_allocation_that_fails_gets_the_kept_blocks_first(tmp_path):
     CHECK(c.alloc(&p, 8 * GB) == hipErrorOutOfMemory);
     CHECK(c.take(&b, 8 * GB) == hipErrorOutOfMemory && !b.ptr);
 """)
+
+
+def test_kept_blocks_go_when_others_fill_the_device_and_on_request(tmp_path):
+    run(tmp_path, r"""
+    DeviceBlock a, b, x;
+    void* others = nullptr;
+    CHECK(c.take(&a, 64 * MB) == hipSuccess && c.take(&b, 64 * MB) == hipSuccess);
+    c.put(a);
+    CHECK(hipMalloc(&others, 40 * GB) == hipSuccess);          // another allocator
+    CHECK(c.take(&x, 128 * MB) == hipSuccess);                 // finds none: the kept block goes
+    CHECK(model::frees == 1);
+    hipFree(others);
+    c.put(b);
+    CHECK(model::frees == 2 && c.take(&a, 512 * MB) == hipSuccess);
+    CHECK(hipMalloc(&others, 40 * GB) == hipSuccess);
+    c.put(x);                                                  // and so does b
+    CHECK(model::frees == 4 && !model::live.count(b.ptr) && !model::live.count(x.ptr));
+    hipFree(others);
+    c.put(a);
+    CHECK(model::frees == 5 && model::live.count(a.ptr));
+    c.clear();
+    CHECK(model::frees == 6 && model::live.empty());
+""")
+
+
+def test_nothing_is_kept_or_handed_out_under_a_byte_limit(tmp_path):
+    run(tmp_path, r"""
+    DeviceBlock a, b;
+    CHECK(c.take(&a, 64 * MB) == hipSuccess);
+    c.put(a);
+    CHECK(model::frees == 0);
+    setenv("TFOCUS_MAX_DEVICE_BYTES", "1000000000", 1);
+    CHECK(c.take(&b, 60 * MB) == hipSuccess && b.bytes == 60 * MB && b.ptr != a.ptr);
+    c.put(b);
+    CHECK(model::frees == 1 && !model::live.count(b.ptr));
+""")
