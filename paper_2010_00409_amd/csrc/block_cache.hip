@@ -94,10 +94,20 @@ void BlockCache::put(const DeviceBlock& block) {
     if (dev != block.dev) (void)hipSetDevice(dev);
 }
 
+// Waits for all streams of the current device as every hipFree does (its
+// implicit synchronisation, whatever is freed: measured with another stream
+// busy).  hipDeviceSynchronize would invalidate a graph capture that another
+// thread has under way, and every later one there.
+static hipError_t wait_for_device() {
+    void* p = nullptr;
+    const hipError_t e = hipMalloc(&p, 256);
+    return e == hipSuccess ? hipFree(p) : e;
+}
+
 // put() with the block's device current.
 void BlockCache::put_current(const DeviceBlock& block) {
     size_t avail = 0, total = 0;
-    if (block.bytes < CACHE_MIN_BLOCK || limited() || hipDeviceSynchronize() != hipSuccess ||
+    if (block.bytes < CACHE_MIN_BLOCK || limited() || wait_for_device() != hipSuccess ||
         hipMemGetInfo(&avail, &total) != hipSuccess || block.bytes > total / 8) {
         (void)hipFree(block.ptr);
         return;

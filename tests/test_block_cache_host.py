@@ -30,7 +30,7 @@ inline size_t next = 4096;
 inline hipError_t hipGetDevice(int* d) { *d = model::current; return hipSuccess; }
 inline hipError_t hipSetDevice(int d) { model::current = d; return hipSuccess; }
 inline hipError_t hipGetLastError() { return hipSuccess; }
-inline hipError_t hipDeviceSynchronize() { ++model::syncs[model::current]; return hipSuccess; }
+inline hipError_t hipDeviceSynchronize() { std::puts("breaks other threads' captures"); std::exit(3); }
 inline hipError_t hipMemGetInfo(size_t* avail, size_t* total) {
     *total = model::TOTAL;
     *avail = model::TOTAL - model::used[model::current];
@@ -49,8 +49,9 @@ inline hipError_t hipFree(void* p) {
     auto it = model::live.find(p);
     if (it == model::live.end()) { std::puts("free of an address that is not live"); std::exit(3); }
     model::used[it->second.dev] -= it->second.bytes;
+    ++model::syncs[it->second.dev];
+    model::frees += it->second.bytes >= 4096;       // blocks, not what put() frees to wait
     model::live.erase(it);
-    ++model::frees;
     return hipSuccess;
 }
 """
