@@ -38,8 +38,9 @@ void BlockCache::clear() {
 hipError_t BlockCache::alloc(void** ptr, size_t bytes) {
     hipError_t e = hipMalloc(ptr, bytes);
     if (e != hipErrorOutOfMemory) return e;
+    // tried again also where nothing is kept any more: another thread may have
+    // given the blocks back since
     std::lock_guard<std::mutex> lk(mu_);
-    if (free_.empty()) return e;
     (void)hipGetLastError();
     clear_locked();
     return hipMalloc(ptr, bytes);

@@ -26,6 +26,9 @@ inline std::map<void*, Alloc> live;             // fake addresses: never read or
 inline size_t used[NDEV];
 inline int current = 0, syncs[NDEV], frees = 0;
 inline size_t next = 4096;
+inline int inside = 0;
+struct Inside { Inside() { ++inside; } ~Inside() { --inside; } };
+inline void (*on_failure)() = nullptr;          // what another thread does right after a failure
 }
 inline hipError_t hipGetDevice(int* d) { *d = model::current; return hipSuccess; }
 inline hipError_t hipSetDevice(int d) { model::current = d; return hipSuccess; }
@@ -37,8 +40,12 @@ inline hipError_t hipMemGetInfo(size_t* avail, size_t* total) {
     return hipSuccess;
 }
 inline hipError_t hipMalloc(void** p, size_t b) {
+    model::Inside in;
     *p = nullptr;
-    if (model::used[model::current] + b > model::TOTAL) return hipErrorOutOfMemory;
+    if (model::used[model::current] + b > model::TOTAL) {
+        if (model::on_failure) model::on_failure();
+        return hipErrorOutOfMemory;
+    }
     *p = reinterpret_cast<void*>(model::next);
     model::next += b;
     model::live[*p] = {model::current, b};
@@ -67,19 +74,19 @@ int main() {
 """
 
 
-def run(tmp_path, body, env=None):
+def run(tmp_path, body, head=""):
     if not shutil.which("g++"):
         pytest.skip("no host compiler")
     inc = tmp_path / "hip"
     inc.mkdir()
     (inc / "hip_runtime.h").write_text(MODEL)
     main = tmp_path / "main.cc"
-    main.write_text(HEAD + body + "    return 0;\n}\n")
+    main.write_text('#include "block_cache.h"\n' + head + HEAD + body + "    return 0;\n}\n")
     exe = str(tmp_path / "main")
     r = subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-I", str(tmp_path), "-I", CSRC, "-x", "c++", str(main),
                         os.path.join(CSRC, "block_cache.hip"), "-o", exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
-    r = subprocess.run([exe], capture_output=True, text=True, env=dict(os.environ, **(env or {})))
+    r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
 
 
@@ -184,4 +191,15 @@ def test_nothing_is_kept_or_handed_out_under_a_byte_limit(tmp_path):
     CHECK(c.take(&b, 60 * MB) == hipSuccess && b.bytes == 60 * MB && b.ptr != a.ptr);
     c.put(b);
     CHECK(model::frees == 1 && !model::live.count(b.ptr));
+""")
+
+
+def test_a_failed_allocation_is_tried_again_after_another_thread_gave_the_blocks_back(tmp_path):
+    run(tmp_path, r"""
+    DeviceBlock a;
+    void* p = nullptr;
+    CHECK(c.take(&a, 8 * GB) == hipSuccess);
+    c.put(a);
+    model::on_failure = [] { model::on_failure = nullptr; BlockCache::get().clear(); };
+    CHECK(c.alloc(&p, 60 * GB) == hipSuccess && p);
 """)
