@@ -1,6 +1,7 @@
 #include "block_cache.h"
 
 #include <cstdlib>
+#include <new>
 
 namespace tf {
 namespace host {
@@ -130,7 +131,11 @@ void BlockCache::put_current(const DeviceBlock& block) {
             ++i;
         }
     }
-    free_.push_back({block, 0});
+    try {
+        free_.push_back({block, 0});
+    } catch (const std::bad_alloc&) {        // called from the C entry points
+        (void)hipFree(block.ptr);
+    }
 }
 
 }  // namespace host

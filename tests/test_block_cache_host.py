@@ -203,3 +203,24 @@ def test_a_failed_allocation_is_tried_again_after_another_thread_gave_the_blocks
     model::on_failure = [] { model::on_failure = nullptr; BlockCache::get().clear(); };
     CHECK(c.alloc(&p, 60 * GB) == hipSuccess && p);
 """)
+
+
+def test_no_exception_leaves_the_cache_when_host_memory_is_out(tmp_path):
+    run(tmp_path, r"""
+    DeviceBlock a;
+    CHECK(c.take(&a, 64 * MB) == hipSuccess);
+    fail_new = true;
+    c.put(a);
+    fail_new = false;
+    CHECK(model::frees == 1 && !model::live.count(a.ptr));
+""", head=r"""
+#include <cstdlib>
+#include <new>
+static bool fail_new = false;
+void* operator new(std::size_t n) {
+    if (fail_new && !model::inside) throw std::bad_alloc();
+    return std::malloc(n);
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, std::size_t) noexcept { std::free(p); }
+""")
