@@ -288,7 +288,7 @@ tf_status tf_get_grid(const tf_solver* s, tf_grid* grid);
  * capture, tight serving loops, harnesses that forbid hipMalloc): the steps of
  * tf_advance applied in place to a caller-owned state, with no allocation and
  * no solver object.  state_dev: [6][nz][ny][nx] of the precision's element
- * type, device memory on the current device; advanced by nsteps steps of dt
+ * type, device memory on the current device, aligned to its elements; advanced by nsteps steps of dt
  * (Eqs. (3)-(4) between forward and inverse 3-D FFTs, the conventions of
  * tf_advance); project_b_first = 1 also removes the longitudinal part of B in
  * the first step, as the first tf_advance after tf_set_pulse does.  Kernel
