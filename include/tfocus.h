@@ -243,8 +243,9 @@ tf_status tf_advance(tf_solver* s, int64_t nsteps, double dt);
  * [component][z][y][x] (jx, jy, jz), x fastest, on the host (j_on_device =
  * 0; the call then waits for the copy) or on the solver's device (1),
  * borrowed for the call.  The first call allocates the current's half spectrum
- * (6 nx ny nz / 2 elements) and, for host or not 16-byte aligned j, a copy of
- * the current (3 nx ny nz elements), kept until tf_destroy; the check against
+ * (6 nx ny nz / 2 elements) and, unless j is 16-byte aligned memory of the
+ * solver's device, a copy of the current (3 nx ny nz elements), kept until
+ * tf_destroy; the check against
  * TFOCUS_MAX_DEVICE_BYTES counts 12 nx ny nz elements.  t += dt.  Asynchronous
  * on the solver's stream for device j.
  * TF_EUNSUPPORTED where nine z columns do not fit the LDS (float64 with

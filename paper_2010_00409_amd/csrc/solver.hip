@@ -17,6 +17,17 @@
 
 namespace {
 using namespace tf::host;
+
+// Whether p is memory of the device that kernels may read: not host memory, nor
+// another device's, which a copy takes and a kernel may not reach.
+bool readable_on(const void* p, int dev) {
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice && a.device == dev;
+}
 }  // namespace
 
 std::string& tf::host::last_error() {
@@ -613,9 +624,9 @@ tf_status tf_advance_current(tf_solver* s, const void* j, int32_t j_on_device, d
                                          " elements in LDS (float64: nz <= 768)");
     const size_t bytes6 = 6 * (size_t)s->cells * s->esize;
     const size_t spec_b = (size_t)s->grid.nz * s->grid.ny * s->nkx * 6 * 2 * s->esize;
-    // the current itself is copied only from the host, or from a device array
-    // that the x pass's 16-byte loads would find misaligned
-    const bool stage = !j_on_device || reinterpret_cast<uintptr_t>(j) % 16 != 0;
+    // the current itself is copied only where the x pass cannot read it in
+    // place, or would read it at the price of misaligned 16-byte loads
+    const bool stage = !j_on_device || reinterpret_cast<uintptr_t>(j) % 16 != 0 || !readable_on(j, s->state_block.dev);
     if (!s->jspec || (stage && !s->jstate)) {
         const size_t have = bytes6 + spec_b + 2 * s->esize * (size_t)(s->grid.nx + s->grid.ny + s->grid.nz);
         if (have + bytes6 + spec_b > device_cap())
