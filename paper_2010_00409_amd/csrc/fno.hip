@@ -467,6 +467,8 @@ struct GradArgs {
 template <typename FA, typename FB>
 __global__ __launch_bounds__(64) void k_wgrad(GradArgs a) {
     constexpr int DEPTH = 8, TA = FA::TILES, TB = FB::TILES;
+    static_assert(N3 % CHUNK == 0 && CHUNK % (16 * DEPTH) == 0, "whole chunks of whole steps");
+    static_assert((HID + 1) * NOUT <= (C + 1) * HID, "the sums of every weight fit the buffer of [P1; c1]");
     const int t = threadIdx.x & 31, grp = threadIdx.x >> 5;
     const int tile0 = 2 * blockIdx.x, k0 = blockIdx.y * CHUNK;
     const char* A = (const char*)a.a + blockIdx.z * a.a_b;
@@ -717,6 +719,7 @@ inline int lines_per_wave(int lines) {
 // order in which those read them (rows of all nodes put every row of a fragment
 // on a page of its own).
 constexpr int HB = 16;                    // nodes per block of the stored hidden layer
+static_assert(CHUNK % HB == 0, "a chunk of nodes is whole blocks");
 struct ProjArgs {
     const float* v;       // [B][N3][32]
     const bf16* p1;       // [32][128]
@@ -1515,11 +1518,11 @@ __global__ void k_scale(float* x, int64_t n, float s) {
 
 using host::fail;
 
-inline Ix plain(int s) { return Ix{30, 0, s}; }
-inline Ix two(int sh, int hi, int lo) { return Ix{sh, hi, lo}; }
+constexpr Ix plain(int s) { return Ix{30, 0, s}; }
+constexpr Ix two(int sh, int hi, int lo) { return Ix{sh, hi, lo}; }
 
 // largest element offset an operand touches (all strides non-negative)
-inline int64_t max_ix(Ix a, int n) {
+constexpr int64_t max_ix(Ix a, int n) {
     if (n <= 0) return 0;
     const int64_t mask = (int64_t(1) << a.sh) - 1;
     return int64_t((n - 1) >> a.sh) * a.hi + std::min<int64_t>(n - 1, mask) * a.lo;
@@ -1725,17 +1728,32 @@ Gemm g_xcontract(const float* A, const float* in, float* out, int B) {
                res(out, plain(C), two(5, 2 * LINE, 1), 0, X1_SZ), 24, N * N * C, N};
     return Gemm{g, 1, B, launch<32, 128, 4, float, float, true, 1>};
 }
+// Whether rows k < n of ny matrices y apart, LINE columns each, lie in a sample
+// of `size` elements (the buffers hold whole samples, and check_batch bounds
+// their number).
+constexpr bool axis_fits(Ix k, int n, int64_t y, int ny, int64_t size) {
+    return (ny - 1) * y + max_ix(k, n) + LINE <= size;
+}
+
+// One y or z transform: the layouts of its operands, checked as it is compiled.
+template <int M_, int K_, int NY> struct AxisLayout {
+    Ix in_k, out_r;
+    int64_t in_y, in_b, out_y, out_b;
+    constexpr bool fits() const {
+        return axis_fits(in_k, K_, in_y, NY, in_b) && axis_fits(out_r, M_, out_y, NY, out_b);
+    }
+};
+
 // The y and z transforms of B samples.  MT = all row tiles of A per wave reads
 // the input once (batch 64, the twelve of a pass: 2.14 ms through k_gemm, 1.79
 // so, 5.1 TB/s); below FEW waves (one per SIMD) the tiles go to waves of their
 // own, which share the columns through the L1 (batch 1: 11 -> 6.7 us each).
-template <int M, int K>
-tf_status axis(tf_fno* f, const float* A, const float* in, float* out, int ny, Ix in_k, Ix out_r, int64_t in_y,
-               int64_t in_b, int64_t out_y, int64_t out_b, int B) {
+template <int M, int K, int NY>
+tf_status axis(tf_fno* f, const float* A, const float* in, float* out, const AxisLayout<M, K, NY>& l, int B) {
     constexpr int MTOT = (M + 31) / 32, FEW = 1024;
     const auto hi = [](Ix x) { return x.sh == 1 ? x.hi : 2 * x.lo; };
-    AxisArgs a{A, in, out, hi(in_k), in_k.lo, hi(out_r), out_r.lo, in_y, in_b, out_y, out_b, ny, 0};
-    const int cols = B * ny * (LINE / 32);
+    AxisArgs a{A, in, out, hi(l.in_k), l.in_k.lo, hi(l.out_r), l.out_r.lo, l.in_y, l.in_b, l.out_y, l.out_b, NY, 0};
+    const int cols = B * NY * (LINE / 32);
     const auto go = [&](auto kernel, int items) {
         a.nitems = items;
         // at most four blocks per CU: a wave takes several items, and A is split less often
@@ -1747,23 +1765,29 @@ tf_status axis(tf_fno* f, const float* A, const float* in, float* out, int ny, I
 }
 // y contraction (per z): X1 layout in, X2 layout out; A is 48 x 128
 tf_status ycontract(tf_fno* f, const float* A, const float* in, float* out, int B) {
-    return axis<48, 128>(f, A, in, out, N, plain(LINE), two(1, N * 2 * LINE, LINE), int64_t(N) * 2 * LINE, X1_SZ,
-                         2 * LINE, X2_SZ, B);
+    constexpr AxisLayout<48, 128, N> l{plain(LINE), two(1, N * 2 * LINE, LINE), int64_t(N) * 2 * LINE, X1_SZ, 2 * LINE,
+                                       X2_SZ};
+    static_assert(l.fits());
+    return axis(f, A, in, out, l, B);
 }
 // z contraction (per ky): X2 layout in, mode layout out
 tf_status zcontract(tf_fno* f, const float* A, const float* in, float* out, int B) {
-    return axis<48, 128>(f, A, in, out, KS, plain(LINE), plain(KS * LINE), int64_t(N) * 2 * LINE, X2_SZ, LINE, X3_SZ,
-                         B);
+    constexpr AxisLayout<48, 128, KS> l{plain(LINE), plain(KS * LINE), int64_t(N) * 2 * LINE, X2_SZ, LINE, X3_SZ};
+    static_assert(l.fits());
+    return axis(f, A, in, out, l, B);
 }
 // z expansion (per ky): mode layout in, X2 layout out; A is 128 x 48
 tf_status zexpand(tf_fno* f, const float* A, const float* in, float* out, int B) {
-    return axis<128, 48>(f, A, in, out, KS, plain(KS * LINE), plain(LINE), LINE, X3_SZ, int64_t(N) * 2 * LINE, X2_SZ,
-                         B);
+    constexpr AxisLayout<128, 48, KS> l{plain(KS * LINE), plain(LINE), LINE, X3_SZ, int64_t(N) * 2 * LINE, X2_SZ};
+    static_assert(l.fits());
+    return axis(f, A, in, out, l, B);
 }
 // y expansion (per z): X2 layout in, X1 layout out
 tf_status yexpand(tf_fno* f, const float* A, const float* in, float* out, int B) {
-    return axis<128, 48>(f, A, in, out, N, two(1, N * 2 * LINE, LINE), plain(LINE), 2 * LINE, X2_SZ,
-                         int64_t(N) * 2 * LINE, X1_SZ, B);
+    constexpr AxisLayout<128, 48, N> l{two(1, N * 2 * LINE, LINE), plain(LINE), 2 * LINE, X2_SZ, int64_t(N) * 2 * LINE,
+                                       X1_SZ};
+    static_assert(l.fits());
+    return axis(f, A, in, out, l, B);
 }
 
 // x-lines of B samples
