@@ -39,7 +39,7 @@ METRIC = "PSATD cell-updates/s + HBM GB/s at 512^3 FP32; surrogate speedup at 1e
 PASS_BYTES_PER_CELL = {"f32": 48, "f64": 96}   # read + write of six components
 
 
-def pass_kernels(plan, nz):
+def pass_kernels(plan, nz, prec="f32"):
     """Kernel (rocprofv3 short name) behind each pass of a step under a kernel
     plan (row_block, fast, zvariant, ...) with nz-point z columns."""
     _, fast, zv = plan[:3]
@@ -47,7 +47,10 @@ def pass_kernels(plan, nz):
         z, col = "k_z", "k_col"
     else:
         waves = {512: "k_z_wave", 256: "k_z_wave256"}
-        z = waves[nz] if zv >= 7 and nz in waves else "k_z_fast" if nz in (128, 192, 256, 512) else "k_z_res"
+        if prec == "f64" or nz not in (128, 192, 256, 512):
+            z = "k_z_res"
+        else:
+            z = waves[nz] if zv >= 7 and nz in waves else "k_z_fast"
         col = "k_col_fast"
     # x_inverse: all but the last launch of a run are k_x_pair, which goes on to
     # the next step's forward transform
@@ -447,7 +450,7 @@ def main():
     per_launch_s = dom_ms / dom_n / 1e3
     alg_bytes = PASS_BYTES_PER_CELL[prec] * cells
     achieved = alg_bytes / per_launch_s / 1e9
-    kernels = pass_kernels(tf.tf_kernel_plan(grid, prec), n[2])
+    kernels = pass_kernels(tf.tf_kernel_plan(grid, prec), n[2], prec)
     traffic = traffic_record(kernels[dom])
     step_ms = sum(passes[k][0] for k in step_passes) / (steps * args.steps)
     # within a run the inverse x pass of a step and the forward one of the next
