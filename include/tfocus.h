@@ -375,8 +375,9 @@ tf_status tf_kernel_plan(const tf_grid* grid, int32_t precision, int32_t* row_bl
                          int32_t* zvariant, int32_t* ystrip);
 
 /* For each cube size N in sizes[0..n): time a few steps of every kernel
- * plan (y row blocking 8 or none; generic kernels or the fast float32
- * kernels with each z strip shape of that length and both y strip widths)
+ * plan (y row blocking 8 or none; generic kernels or the fast ones, at the
+ * lengths with tuned float32 kernels with each z strip shape of that length and
+ * both y strip widths)
  * on the current device with HIP events, on pseudo-random fields, in three
  * interleaved rounds (each plan keeps its fastest round); keep the fastest
  * plan and merge "arch precision N N N row_block fast zvariant ystrip ms"

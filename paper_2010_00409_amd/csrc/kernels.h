@@ -70,6 +70,15 @@ struct Batch {
     const double* cdt = nullptr;
 };
 
+// Axis lengths whose float32 y and z passes have kernels that a plan chooses
+// among; every other length, and float64, has one of each beside the generic
+// kernels.
+constexpr bool tuned_length(int n) { return n == 64 || n == 128 || n == 192 || n == 256 || n == 512; }
+// z variants of a tuned length: lengths of one lane group (64) have one kernel;
+// variants 7 to 9 and 11 (one wave per mode) exist for 512-point z columns, 7
+// and 8 for 256-point ones, and elsewhere run variant 6.
+constexpr int z_variants(int n) { return n == 512 ? 12 : n == 256 ? 9 : tuned_length(n) && n > 64 ? 7 : 1; }
+
 // Forward x pass: real state [6][nz][ny][nx] -> spectral (x transformed).
 template <typename T> hipError_t launch_x_forward(const T* real, void* spec, const void* tw,
                                                   int nx, int ny, int nz, RowMap rm, Batch bt, hipStream_t st);
