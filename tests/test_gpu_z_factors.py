@@ -18,13 +18,13 @@ D = 0.31
 DTS = [0.37 * (i + 1) for i in range(24)] + [-0.83, 517.3, 2.0e4]
 
 
-@pytest.mark.parametrize("nx,nz", [(48, 24), (48, 48)] + [(NX, n) for n in (16, 32, 64, 96, 128, 192, 256, 384, 512,
-                                                                           768, 1024)])
-def test_factors_are_rounded_float64_values(nx, nz):
-    g = dict(nx=nx, ny=NY, nz=nz, dx=D, dy=D, dz=D, x_min=0.0, y_min=0.0, z_min=0.0)
-    state = np.zeros((6, nz, NY, nx), dtype=np.float32)
+@pytest.mark.parametrize("nx,ny,nz", [(48, 64, 24), (48, 8, 48)]
+                         + [(NX, NY, n) for n in (16, 32, 64, 96, 128, 192, 256, 384, 512, 768, 1024)])
+def test_factors_are_rounded_float64_values(nx, ny, nz):
+    g = dict(nx=nx, ny=ny, nz=nz, dx=D, dy=D, dz=D, x_min=0.0, y_min=0.0, z_min=0.0)
+    state = np.zeros((6, nz, ny, nx), dtype=np.float32)
     state[0, 0::4], state[0, 2::4] = 1.0, -1.0
-    cells = nx * NY * nz
+    cells = nx * ny * nz
     a, sc = np.float32(cells // 2), np.float32(1.0 / cells)
     out = np.empty_like(state)
     with tf.Solver(g, "f32") as s:
