@@ -883,7 +883,8 @@ __global__ __launch_bounds__(256, BWD ? 3 : 4) void k_proj(ProjArgs a) {
 __device__ __forceinline__ float coord(int i) { return float(i - N / 2) / float(N / 2); }
 
 // v0[b][node][c] = b0[c] + sum_i p[b][i] W0[i][c] + x W0[8][c] + y W0[9][c] + z W0[10][c],
-// always summed in this order
+// summed in this order, each coordinate's product fused into the sum (k_lift_x
+// rounds some of them first, see there)
 __device__ __forceinline__ float lift_base(const float* pb, const float* w0, const float* b0, int c) {
     float s = b0[c];
     for (int i = 0; i < NPAR; ++i) s += pb[i] * w0[i * C + c];
@@ -900,8 +901,8 @@ __device__ __forceinline__ float lift_at(float base, const float* w0, int c, int
     return lift_term(lift_term(lift_term(base, w0[8 * C + c], x), w0[9 * C + c], y), w0[10 * C + c], z);
 }
 
-// One block per (z, y) pair of lines: a thread keeps four channels and walks two
-// lines of nodes in 16-byte stores.  16 samples: 330 us with one element per
+// One block per LIFT_LINES lines of one z: a thread keeps four channels and walks
+// the lines two nodes each in 16-byte stores.  16 samples: 330 us with one element per
 // thread, each summing its base anew, 88 so (537 MB).
 constexpr int LIFT_LINES = 8;             // lines per block (64 divides into them)
 __global__ __launch_bounds__(256) void k_lift(const float* p, const float* w0, const float* b0, float* v) {
@@ -969,9 +970,11 @@ struct InfArgs {
 //   X1[(s,kx)][c] = sum_x Fx[(s,kx)][x] v0[x][c]    (split bf16)
 // Batch 64: 305 us with the matrix split by every wave, 149 so (805 MB written,
 // 165 us at a copy's rate).  The y and z terms of the lift are fused into the
-// sum for x < 16 and rounded first beyond: the windows of a trained surrogate
-// stay the same bits that this operator has always given (a float32 rounding
-// here can flip a bf16 one in the mixing, 1e-4 of the output).
+// sum for x < 16 and rounded first beyond.  Either is as accurate, and no rule of
+// the method chooses between them; this is the mixture that the windows of
+// surrogates trained so far were computed and their errors quoted with, and
+// another one moves outputs by up to 1e-4 (a float32 rounding here can flip a
+// bf16 one in the mixing).
 __global__ __launch_bounds__(256) void k_lift_x(InfArgs a) {
     __shared__ bf16x8 fx[4][2][64];
     const int lane = threadIdx.x & 63, t = lane & 31, grp = lane >> 5;
