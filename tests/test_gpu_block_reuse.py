@@ -80,8 +80,8 @@ def test_blocks_pass_between_streams_and_between_solvers_and_batches():
             dst = torch.empty((1, 6, 32, 32, 32), dtype=torch.float32, device="cuda")
         with tf.Batch([grid()], [p], "f32", st) as b:
             b.run([2], [0.5 * P["R0"]], win, dst)
-            st.synchronize()
-            out = dst[0].cpu().numpy()
+            with torch.cuda.stream(st):
+                out = dst[0].cpu().numpy()
             b.run([20], [0.1], win, dst)                             # still running when the batch goes
         return out
 
@@ -124,8 +124,9 @@ def test_objects_may_go_while_another_thread_captures():
         done.set()
 
     def goes():
+        st = torch.cuda.Stream()
         while not done.is_set():
-            with tf.Solver(grid(), "f32"):
+            with tf.Solver(grid(), "f32", st):
                 count[0] += 1
 
     ts = [threading.Thread(target=f) for f in (captures, goes)]
